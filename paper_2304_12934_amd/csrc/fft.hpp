@@ -105,7 +105,9 @@ constexpr bool radix_plan_complete(int L) { return span_before(L, num_passes(L))
 // small DFTs, X_k = sum_n x_n exp(-+2 pi i n k / R)
 // ---------------------------------------------------------------------------
 
-template <int R, bool INV>
+// HALF: only the inputs n < R/4 and n >= 3R/4 are non-zero (the others are
+// not read).
+template <int R, bool INV, bool HALF = false>
 struct Dft;
 
 template <bool INV>
@@ -130,12 +132,27 @@ struct Dft<4, INV> {
 };
 
 template <bool INV>
-struct Dft<8, INV> {
+struct Dft<4, INV, true> {
+  __device__ __forceinline__ static void run(float2* v) {
+    const float2 a = v[0];
+    // (inputs that are products are rounded here, by the addition of zero, and
+    // enter fused only where they did in the transform with zeros: v[1], v[3])
+    const float2 r = round_product(v[0]), d = round_product(v[3]), q = mul_i<INV>(d);
+    v[0] = c_add(r, d);
+    v[2] = c_sub(r, d);
+    v[1] = c_sub(a, q);
+    v[3] = c_add(a, q);
+  }
+  __device__ __forceinline__ static float2 round_product(float2 x) { return make_float2(x.x + 0.f, x.y + 0.f); }
+};
+
+template <bool INV, bool HALF>
+struct Dft<8, INV, HALF> {
   __device__ __forceinline__ static void run(float2* v) {
     float2 e[4] = {v[0], v[2], v[4], v[6]};
     float2 o[4] = {v[1], v[3], v[5], v[7]};
-    Dft<4, INV>::run(e);
-    Dft<4, INV>::run(o);
+    Dft<4, INV, HALF>::run(e);
+    Dft<4, INV, HALF>::run(o);
     const float h = 0.70710678118654752440f;
     // W^1 = (1 -+ i)/sqrt(2), W^2 = -+i, W^3 = W^2 W^1
     const float2 o1 = INV ? make_float2((o[1].x - o[1].y) * h, (o[1].x + o[1].y) * h)
@@ -235,8 +252,9 @@ __device__ __forceinline__ float2 mul_root(float2 a, int m) {
 // N = P*Q point DFT from P- and Q-point ones: input n = Q*n1 + n2, output
 // k = k1 + P*k2; DFT_P over n1 for each n2, twiddles W_N^(n2*k1), DFT_Q over
 // n2 for each k1.
-template <int P, int Q, bool INV>
+template <int P, int Q, bool INV, bool HALF = false>
 struct DftPQ {
+  static_assert(!HALF || P == 4, "the zero inputs are whole quarters of the first stage");
   __device__ __forceinline__ static void run(float2* v) {
     float2 y[Q][P];
 #pragma unroll
@@ -244,7 +262,7 @@ struct DftPQ {
       float2 t[P];
 #pragma unroll
       for (int n1 = 0; n1 < P; ++n1) t[n1] = v[Q * n1 + n2];
-      Dft<P, INV>::run(t);
+      Dft<P, INV, HALF>::run(t);
 #pragma unroll
       for (int k1 = 0; k1 < P; ++k1) y[n2][k1] = mul_root<P * Q, INV>(t[k1], n2 * k1);
     }
@@ -260,8 +278,8 @@ struct DftPQ {
   }
 };
 
-template <bool INV>
-struct Dft<16, INV> : DftPQ<4, 4, INV> {};
+template <bool INV, bool HALF>
+struct Dft<16, INV, HALF> : DftPQ<4, 4, INV, HALF> {};
 template <bool INV>
 struct Dft<20, INV> : DftPQ<5, 4, INV> {};
 
@@ -284,7 +302,36 @@ constexpr int lds_elems() {
 struct Lds {
   float2* p;
   __device__ __forceinline__ float2& operator[](int i) const { return p[i ^ ((i >> 4) & 15)]; }
+  // Element base + c with c a constant once the calling loop is unrolled, a
+  // multiple of 16: the swizzle of base + c depends on c only through
+  // c / 16 mod 16, so the accesses of one butterfly (or of one thread's strided
+  // loop) share one address per such class and take the rest of c as the
+  // instruction's immediate offset.
+  __device__ __forceinline__ float2& at(int base, int c) const {
+    const int x = (base & ~15) | ((base ^ ((base >> 4) + (c >> 4))) & 15);
+    return p[x + c];
+  }
+  // The same when base and c have no bits in common (and c may be any
+  // constant): the swizzle is linear in the bits of the index, so the low byte
+  // of c enters by one exclusive or and the rest is the immediate offset.
+  __device__ __forceinline__ float2& at_disjoint(int base, int c) const {
+    const int x = ((base ^ ((base >> 4) & 15)) * 8) ^ (((c & 255) ^ ((c >> 4) & 15)) * 8);   // bytes
+    return *reinterpret_cast<float2*>(reinterpret_cast<char*>(p) + x + (c & ~255) * 8);
+  }
 };
+
+constexpr bool is_pow2(int v) { return (v & (v - 1)) == 0; }
+
+// element base + r STEP of a butterfly; DISJOINT: base shares no bits with any r STEP
+template <int STEP, bool DISJOINT>
+__device__ __forceinline__ float2& butterfly_elem(Lds s, int base, int r) {
+  if constexpr (DISJOINT)
+    return s.at_disjoint(base, r * STEP);
+  else if constexpr (STEP % 16 == 0)
+    return s.at(base, r * STEP);
+  else
+    return s[base + r * STEP];
+}
 
 // ---------------------------------------------------------------------------
 // one Stockham pass and the whole transform
@@ -351,7 +398,7 @@ __device__ __forceinline__ void fft_pass(Lds s, TwPtr __restrict__ tw, int tid) 
     const int j = tid + i * T;
     if (NB % T == 0 || j < NB) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[i][r] = s[j + r * NB];
+      for (int r = 0; r < R; ++r) v[i][r] = butterfly_elem<NB, is_pow2(NB)>(s, j, r);
     }
   }
   __syncthreads();
@@ -365,9 +412,10 @@ __device__ __forceinline__ void fft_pass(Lds s, TwPtr __restrict__ tw, int tid) 
         for (int r = 1; r < R; ++r) v[i][r] = c_mul(v[i][r], INV ? c_conj(w[i][r - 1]) : w[i][r - 1]);
       }
       Dft<R, INV>::run(v[i]);
+      // base = k mod Ns below r Ns, a multiple of Ns R above it (0 in the last pass)
       const int base = (j - k) * R + k;
 #pragma unroll
-      for (int r = 0; r < R; ++r) s[base + r * Ns] = v[i][r];
+      for (int r = 0; r < R; ++r) butterfly_elem<Ns, is_pow2(Ns) && (is_pow2(R) || Ns * R == L)>(s, base, r) = v[i][r];
     }
   }
   __syncthreads();
@@ -391,38 +439,75 @@ __device__ __forceinline__ void fft_lds(Lds s, TwPtr __restrict__ tw, int tid) {
   fft_passes<L, T, INV>(s, tw, tid);
 }
 
-// First pass of a transform whose inputs come from load(n) (natural index
-// n) straight into registers; the pass writes the LDS buffer and the
-// workgroup synchronises.  With HALF, the input is a length-L/2 signal
-// zero-padded to L and centred (non-zero only at natural indices [0, L/4)
-// and [3L/4, L)): the zeros of each first-pass butterfly sit at fixed
-// positions and are not loaded.
-template <int L, int T, bool INV, bool HALF, class Load>
-__device__ __forceinline__ void fft_first_pass_from(Lds s, int tid, Load&& load) {
-  constexpr int R = radix_of(L, 0);
-  static_assert(!HALF || (R % 4 == 0 && L % 4 == 0), "the first radix must split the zero padding evenly");
-  constexpr int NB = L / R;
-  constexpr int PER = (NB + T - 1) / T;
+// A thread's butterflies of pass P in registers.
+template <int L, int T, int P>
+struct Regs {
+  static constexpr int R = radix_of(L, P), NB = L / R, PER = (NB + T - 1) / T;
+  float2 v[PER][R];
+};
+
+// The first pass takes its inputs from load(j, r) (input r of butterfly j,
+// natural index j + r L/R; r is a constant once the loop is unrolled) straight
+// into registers, and the workgroup synchronises after it.  With HALF, the
+// input is a length-L/2 signal zero-padded to L and centred (non-zero only at
+// natural indices [0, L/4) and [3L/4, L)): the zeros of each first-pass
+// butterfly sit at fixed positions (inputs R/4 .. 3R/4 - 1), are not loaded and
+// take no additions.
+
+// Inputs of the first pass in registers.
+template <int L, int T, class Load>
+__device__ __forceinline__ void first_inputs(Regs<L, T, 0>& a, int tid, Load&& load) {
+  constexpr int R = radix_of(L, 0), NB = L / R;
 #pragma unroll
-  for (int i = 0; i < PER; ++i) {
+  for (int i = 0; i < Regs<L, T, 0>::PER; ++i) {
     const int j = tid + i * T;
     if (NB % T == 0 || j < NB) {
-      // input r of butterfly j is index j + r NB: with HALF, below L/4 for
-      // r < R/4, at or above 3L/4 for r >= 3R/4, padding in between
+#pragma unroll
+      for (int r = 0; r < R; ++r) a.v[i][r] = load(j, r);
+    }
+  }
+}
+
+// The first pass of the inputs in a, written to the LDS buffer.
+template <int L, int T, bool INV>
+__device__ __forceinline__ void first_pass_to_lds(Lds s, int tid, Regs<L, T, 0>& a) {
+  constexpr int R = radix_of(L, 0), NB = L / R;
+#pragma unroll
+  for (int i = 0; i < Regs<L, T, 0>::PER; ++i) {
+    const int j = tid + i * T;
+    if (NB % T == 0 || j < NB) {
+      Dft<R, INV>::run(a.v[i]);
+#pragma unroll
+      for (int r = 0; r < R; ++r) butterfly_elem<1, is_pow2(R)>(s, j * R, r) = a.v[i][r];
+    }
+  }
+  __syncthreads();
+}
+
+// Both in one, a butterfly's loads next to its additions: a load that returns a
+// product is then fused into them.
+template <int L, int T, bool INV, bool HALF, class Load>
+__device__ __forceinline__ void fft_first_pass_from(Lds s, int tid, Load&& load) {
+  constexpr int R = radix_of(L, 0), NB = L / R;
+  static_assert(!HALF || (R % 4 == 0 && L % 4 == 0), "the first radix must split the zero padding evenly");
+#pragma unroll
+  for (int i = 0; i < (NB + T - 1) / T; ++i) {
+    const int j = tid + i * T;
+    if (NB % T == 0 || j < NB) {
       float2 v[R];
 #pragma unroll
       for (int r = 0; r < R; ++r)
-        v[r] = (!HALF || r < R / 4 || r >= 3 * R / 4) ? load(j + r * NB) : make_float2(0.f, 0.f);
-      Dft<R, INV>::run(v);
+        v[r] = (!HALF || r < R / 4 || r >= 3 * R / 4) ? load(j, r) : make_float2(0.f, 0.f);
+      Dft<R, INV, HALF>::run(v);
 #pragma unroll
-      for (int r = 0; r < R; ++r) s[j * R + r] = v[r];
+      for (int r = 0; r < R; ++r) butterfly_elem<1, is_pow2(R)>(s, j * R, r) = v[r];
     }
   }
   __syncthreads();
 }
 
 // Transform of a length-L/2 signal zero-padded to L and centred, its input
-// from load(n): the first pass as fft_first_pass_from with HALF, the rest as
+// from load(j, r): the first pass as fft_first_pass_from with HALF, the rest as
 // in fft_lds.  No LDS fill precedes it; on return s holds the result and the
 // workgroup has synchronised.
 template <int L, int T, bool INV, class Load>
@@ -432,10 +517,26 @@ __device__ __forceinline__ void fft_lds_halfzero(Lds s, TwPtr __restrict__ tw, i
   fft_passes<L, T, INV, 1>(s, tw, tid);
 }
 
+// store(j, r, v[r]) for the outputs j + r NS of a last-pass butterfly; with
+// HALF only those at [0, L/4) and [3L/4, L)
+template <int L, int NS, int R, bool HALF, class Store>
+__device__ __forceinline__ void store_kept(int j, const float2 (&v)[R], Store&& store) {
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if constexpr (HALF && R % 4 == 0) {
+      if (r < R / 4 || r >= R - R / 4) store(j, r, v[r]);
+    } else {
+      const int n = j + r * NS;
+      if (!HALF || n < L / 4 || n >= L - L / 4) store(j, r, v[r]);
+    }
+  }
+}
+
 // Transform whose last pass hands its outputs straight from registers to
-// store(n, value) (natural index n) instead of writing the LDS buffer; with
-// HALF only the outputs at [0, L/4) and [3L/4, L) (the centred half of the
-// result) are handed over.  Passes START to the last but one run as in
+// store(j, r, value) (natural index j + r Ns, Ns the span of the last pass,
+// r a constant once the loop is unrolled) instead of writing the LDS buffer;
+// with HALF only the outputs at [0, L/4) and [3L/4, L) (the centred half of
+// the result) are handed over.  Passes START to the last but one run as in
 // fft_lds (START = 1 after fft_first_pass_from).  Expects s to hold the
 // input of pass START and the workgroup synchronised; leaves s holding the
 // input of the last pass, and the caller must synchronise before writing s
@@ -456,18 +557,132 @@ __device__ __forceinline__ void fft_lds_store_out(Lds s, TwPtr __restrict__ tw, 
     if (Ns % T == 0 || j < Ns) {
       float2 v[R], w[R - 1];
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[r] = s[j + r * Ns];
+      for (int r = 0; r < R; ++r) v[r] = butterfly_elem<Ns, is_pow2(Ns)>(s, j, r);
       radix_twiddles<R>(tw, j, w);
 #pragma unroll
       for (int r = 1; r < R; ++r) v[r] = c_mul(v[r], INV ? c_conj(w[r - 1]) : w[r - 1]);
       Dft<R, INV>::run(v);
+      store_kept<L, Ns, R, HALF>(j, v, store);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Split exchange: passes that keep the data in registers and hand it on
+// through an L-float buffer, the real parts first and then the imaginary ones.
+// Half the LDS of Lds for twice the barriers, so that more workgroups are
+// resident.  For the transforms that end in registers (the adjoint's), whose
+// 32 or 40 KB buffers otherwise admit five or four workgroups per CU.
+// Measured on 2560^2 and 2048^2 slices, eight per launch (us per slice):
+// adjoint columns 35.5 -> 33.3 and 21.9 -> 20.0, adjoint rows 24.8 -> 23.0 and
+// 14.4 -> 14.1; shorter lengths, already at the wavefront limit, gain nothing.
+// Element i lives at i ^ ((i >> 5) & 15): the banks of 4-byte elements.
+// ---------------------------------------------------------------------------
+constexpr bool split_exchange_length(int L) { return L == 4096 || L == 5120; }
+
+struct LdsF {
+  float* p;
+  __device__ __forceinline__ float& operator[](int i) const { return p[i ^ ((i >> 5) & 15)]; }
+  // as Lds::at and Lds::at_disjoint; c of at() a multiple of 32
+  __device__ __forceinline__ float& at(int base, int c) const {
+    const int x = (base & ~15) | ((base ^ ((base >> 5) + (c >> 5))) & 15);
+    return p[x + c];
+  }
+  __device__ __forceinline__ float& at_disjoint(int base, int c) const {
+    const int x = ((base ^ ((base >> 5) & 15)) * 4) ^ (((c & 511) ^ ((c >> 5) & 15)) * 4);   // bytes
+    return *reinterpret_cast<float*>(reinterpret_cast<char*>(p) + x + (c & ~511) * 4);
+  }
+};
+template <int STEP, bool DISJOINT>
+__device__ __forceinline__ float& butterfly_elem(LdsF s, int base, int r) {
+  if constexpr (DISJOINT)
+    return s.at_disjoint(base, r * STEP);
+  else if constexpr (STEP % 32 == 0)
+    return s.at(base, r * STEP);
+  else
+    return s[base + r * STEP];
+}
+
+// outputs of pass P (in a) -> inputs of pass P + 1 (in u)
+template <int L, int T, int P>
+__device__ __forceinline__ void split_exchange(LdsF s, int tid, const Regs<L, T, P>& a, Regs<L, T, P + 1>& u) {
+  constexpr int R = radix_of(L, P), Ns = span_before(L, P), NB = L / R;
+  constexpr int R1 = radix_of(L, P + 1), NB1 = L / R1;
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int n = j + r * Ns;
-        if (!HALF || n < L / 4 || n >= L - L / 4) store(n, v[r]);
+  for (int part = 0; part < 2; ++part) {
+    if (part) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < Regs<L, T, P>::PER; ++i) {
+      const int j = tid + i * T;
+      if (NB % T == 0 || j < NB) {
+        const int k = j % Ns;
+        const int base = (j - k) * R + k;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          butterfly_elem<Ns, is_pow2(Ns) && (is_pow2(R) || Ns * R == L)>(s, base, r) = part ? a.v[i][r].y : a.v[i][r].x;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < Regs<L, T, P + 1>::PER; ++i) {
+      const int j = tid + i * T;
+      if (NB1 % T == 0 || j < NB1) {
+#pragma unroll
+        for (int r = 0; r < R1; ++r) {
+          const float t = butterfly_elem<NB1, is_pow2(NB1)>(s, j, r);
+          if (part) u.v[i][r].y = t;
+          else u.v[i][r].x = t;
+        }
       }
     }
   }
+}
+
+// passes P .. last on the outputs a of pass P - 1, then store(j, r, value) as
+// in fft_lds_store_out
+template <int L, int T, int P, bool INV, bool HALF, class Store>
+__device__ __forceinline__ void split_passes(LdsF s, TwPtr __restrict__ tw, int tid, const Regs<L, T, P - 1>& a,
+                                             Store&& store) {
+  constexpr int R = radix_of(L, P), Ns = span_before(L, P), NB = L / R;
+  Regs<L, T, P> u;
+  split_exchange<L, T, P - 1>(s, tid, a, u);
+#pragma unroll
+  for (int i = 0; i < Regs<L, T, P>::PER; ++i) {
+    const int j = tid + i * T;
+    if (NB % T == 0 || j < NB) {
+      const int k = j % Ns;
+      float2 w[R - 1];
+      radix_twiddles<R>(tw, k * (L / (Ns * R)), w);
+#pragma unroll
+      for (int r = 1; r < R; ++r) u.v[i][r] = c_mul(u.v[i][r], INV ? c_conj(w[r - 1]) : w[r - 1]);
+      Dft<R, INV>::run(u.v[i]);
+      if constexpr (P + 1 == num_passes(L)) store_kept<L, NB, R, HALF>(j, u.v[i], store);
+    }
+  }
+  if constexpr (P + 1 < num_passes(L)) {
+    __syncthreads();   // the exchange's last reads are done
+    split_passes<L, T, P + 1, INV, HALF>(s, tw, tid, u, store);
+  }
+}
+
+// The whole transform of the first pass's inputs a, its outputs handed to
+// store(j, r, value) from registers, through lds (L float2; the split exchange
+// uses half of it).
+template <int L, int T, bool INV, bool SPLIT, class Store>
+__device__ __forceinline__ void fft_store_out(float2* lds, TwPtr __restrict__ tw, int tid, Regs<L, T, 0>& a, Store&& store) {
+  static_assert(radix_plan_complete(L), "FFT length must be 2^a * 3^b * 5^c");
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int i = 0; i < Regs<L, T, 0>::PER; ++i) Dft<radix_of(L, 0), INV>::run(a.v[i]);
+    split_passes<L, T, 1, INV, true>(LdsF{reinterpret_cast<float*>(lds)}, tw, tid, a, store);
+  } else {
+    first_pass_to_lds<L, T, INV>(Lds{lds}, tid, a);
+    fft_lds_store_out<L, T, INV, 1>(Lds{lds}, tw, tid, store);
+  }
+}
+template <int L, bool SPLIT>
+constexpr int store_out_lds_elems() {
+  return SPLIT ? L / 2 : lds_elems<L>();
 }
 
 // threads per transform for a length-L FFT.  For 5·2^a lengths five

@@ -50,6 +50,15 @@ namespace nrk {
 // helpers
 // ---------------------------------------------------------------------------
 
+// Constant address space: loads through it are scalar wherever the address is
+// uniform, also after a workgroup has stored (the kernels' arguments, the plan's
+// descriptors, work lists and items never change during a launch).
+#ifdef __HIP_DEVICE_COMPILE__
+#define NR_C __attribute__((address_space(4)))
+#else
+#define NR_C
+#endif
+
 // Coordinates of a polar point j on angle table entry (gx, gy): u = j*(gx, gy)
 // in grid cells, first tap g0 = ceil(u - W/2) and the W weights
 // phi(u - g0 - i) from the piecewise polynomial in z = u - g0 - (W-1)/2.
@@ -114,16 +123,16 @@ struct DSlice {
   NR_G float2* ext;
   NR_G float2* yh;
   const NR_G int32_t* pts;
-  const NR_G SpreadItem* items;
+  const NR_C SpreadItem* items;
   const NR_G int32_t* zero_tiles;
   const NR_G int32_t* ipts;
-  const NR_G SpreadItem* iitems;
+  const NR_C SpreadItem* iitems;
   int itiles_x, rdisc, jbits;
 };
 
 // The slice descriptor by value (uniform: scalar loads).
-__device__ __forceinline__ DSlice load_desc(const SliceDesc* p) {
-  const SliceDesc s = *p;
+__device__ __forceinline__ DSlice load_desc(const SliceDesc* descs, int slice) {
+  const NR_C SliceDesc& s = ((const NR_C SliceDesc*)descs)[__builtin_amdgcn_readfirstlane(slice)];
   DSlice d;
   d.N = s.N, d.Nt = s.Nt, d.na = s.na, d.G = s.G, d.H = s.H, d.rows = s.rows, d.cols = s.cols;
   d.tiles_x = s.tiles_x;
@@ -138,14 +147,27 @@ __device__ __forceinline__ DSlice load_desc(const SliceDesc* p) {
   d.ext = (NR_G float2*)s.ext;
   d.yh = (NR_G float2*)s.yh;
   d.pts = (const NR_G int32_t*)s.pts;
-  d.items = (const NR_G SpreadItem*)s.items;
+  d.items = (const NR_C SpreadItem*)s.items;
   d.zero_tiles = (const NR_G int32_t*)s.zero_tiles;
   d.ipts = (const NR_G int32_t*)s.ipts;
-  d.iitems = (const NR_G SpreadItem*)s.iitems;
+  d.iitems = (const NR_C SpreadItem*)s.iitems;
   d.itiles_x = s.itiles_x;
   d.rdisc = s.rdisc;
   d.jbits = s.jbits;
   return d;
+}
+
+__device__ __forceinline__ SpreadItem load_item(const NR_C SpreadItem* items, int unit) {
+  const NR_C SpreadItem& s = items[__builtin_amdgcn_readfirstlane(unit)];
+  return SpreadItem{s.tile, s.begin, s.end, s.flags, s.bound};
+}
+
+// entry p of a launch's work list ({-1, 0} past its end)
+template <class LA>
+__device__ __forceinline__ WorkItem work_entry(const LA& a, int p) {
+  if (p >= a.n_work) return WorkItem{-1, 0};
+  const NR_C WorkItem& w = ((const NR_C WorkItem*)a.work)[p];
+  return WorkItem{w.slice, w.unit};
 }
 
 // round to the nearest integer, halves up: one instruction (v_cvt_rpi_i32_f32
@@ -246,9 +268,8 @@ struct SpreadLds {
 // b takes entry b; the forward columns, the interpolation and the spreading
 // take two, see there); padding entries (slice < 0) and blocks past the list
 // do nothing.
-#define NR_FOR_EACH_UNIT(a, wi)                                                                    \
-  if (const WorkItem wi = int(blockIdx.x) < (a).n_work ? (a).work[blockIdx.x] : WorkItem{-1, 0}; \
-      wi.slice >= 0)
+#define NR_FOR_EACH_UNIT(a, wi) \
+  if (const WorkItem wi = work_entry(a, int(blockIdx.x)); wi.slice >= 0)
 
 
 // T is stored in tiles of 4 kept frequencies x 2 rows: the row transform's
@@ -256,10 +277,61 @@ struct SpreadLds {
 // threads instead of one 16-byte piece per 20 KB row of T, at the price of
 // 16-byte pieces 64 bytes apart in the column transforms (measured: rows
 // -8 us, adjoint rows -5, columns +6, adjoint columns +3 per 2560^2 slice).
-// Index of the float4 holding rows 2p, 2p+1 at q:
-__device__ __forceinline__ size_t t4(int q, int p, int N) {
-  return (size_t(q >> 2) * (N / 2) + p) * 4 + (q & 3);
+// Index of the float4 holding rows 2p, 2p+1 at q (below 2^24 at the longest
+// row, so byte offsets fit 32 bits: the kernels add them to a uniform base
+// pointer, which the loads and stores take as scalar base + 32-bit offset):
+__device__ __forceinline__ uint32_t t4(int q, int p, int N) {
+  return (uint32_t(q >> 2) * uint32_t(N / 2) + uint32_t(p)) * 4u + uint32_t(q & 3);
 }
+
+// Buffer descriptor of `bytes` bytes at a workgroup-uniform pointer.  A buffer
+// access adds a 32-bit offset per lane and a scalar offset to it, so the
+// accesses of one thread that differ by a constant share one address register
+// and take no address arithmetic (64-bit pointer arithmetic was about a tenth
+// of the transforms' vector instructions); a lane whose own offset lies past
+// `bytes` loads zero.
+#ifdef __HIP_DEVICE_COMPILE__
+using Rsrc = __amdgpu_buffer_rsrc_t;
+#else
+struct Rsrc {};
+#endif
+__device__ __forceinline__ Rsrc buf(const NR_G void* p, uint32_t bytes) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, int(bytes), 0x00020000);
+#else
+  return {};
+#endif
+}
+template <class V>
+__device__ __forceinline__ V buf_load(Rsrc r, uint32_t lane_off, uint32_t off) {
+  V v{};
+#ifdef __HIP_DEVICE_COMPILE__
+  if constexpr (sizeof(V) == 4) v = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(r, int(lane_off), int(off), 0));
+  else if constexpr (sizeof(V) == 8) v = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, int(lane_off), int(off), 0));
+  else v = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, int(lane_off), int(off), 0));
+#endif
+  return v;
+}
+typedef unsigned nr_u2 __attribute__((ext_vector_type(2)));
+typedef unsigned nr_u4 __attribute__((ext_vector_type(4)));
+template <class V>
+__device__ __forceinline__ void buf_store(Rsrc r, uint32_t lane_off, uint32_t off, V v) {
+#ifdef __HIP_DEVICE_COMPILE__
+  if constexpr (sizeof(V) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, int(lane_off), int(off), 0);
+  else if constexpr (sizeof(V) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(nr_u2, v), r, int(lane_off), int(off), 0);
+  // 16 bytes: the constant goes into the lane's offset.  With a scalar offset
+  // register the compiler places no wait state between the store and a vector
+  // instruction that overwrites its data, and stores of such kernels were
+  // seen to pick up the overwritten values.
+  else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(nr_u4, v), r, int(lane_off + off), 0, 0);
+#endif
+}
+// bytes of T for slices of width N = L/2 (its q rows rounded up to whole tiles)
+template <int L>
+constexpr uint32_t t_bytes() {
+  return uint32_t((L / 2 + 4) / 4 * 4) * uint32_t(L / 2) * 8u;
+}
+
 // ---------------------------------------------------------------------------
 // F1: rows (along x), two at a time, transposed store into T
 // ---------------------------------------------------------------------------
@@ -267,28 +339,31 @@ __device__ __forceinline__ size_t t4(int q, int p, int N) {
 template <int L, int T, class LA>
 __device__ __forceinline__ void fwd_rows_unit(const LA& a, const WorkItem wi, float2* sbuf, const int tid) {
   const Lds s{sbuf};
-  const DSlice d = load_desc(a.descs + wi.slice);
+  const DSlice d = load_desc(a.descs, wi.slice);
   constexpr int N = L / 2;   // G = 2N
-  const int iy0 = 2 * wi.unit;
-  const float* __restrict__ f0 = a.vol_in + d.vol_off + size_t(iy0) * N;
+  const int iy0 = 2 * __builtin_amdgcn_readfirstlane(wi.unit);
+  const Rsrc f = buf((const NR_G float*)a.vol_in + d.vol_off + size_t(iy0) * N, 8u * N);
   const float d0 = d.deapod[iy0], d1 = d.deapod[iy0 + 1];
   // x = ix - N/2 sits at index x mod L; indices N/2 .. L - N/2 - 1 are the zero padding
-  const NR_G float* __restrict__ dp = d.deapod;
-  fft_lds_halfzero<L, T, false>(s, d.tw_G, tid, [&](int n) {
-    const int ix = n < N / 2 ? n + N / 2 : n - (L - N / 2);
-    const float dx = dp[ix];
-    return make_float2(dx * d0 * f0[ix], dx * d1 * f0[N + ix]);
+  const Rsrc dp = buf(d.deapod, 4u * N);
+  fft_lds_halfzero<L, T, false>(s, d.tw_G, tid, [&](int j, int r) {
+    constexpr int R = radix_of(L, 0);
+    const uint32_t jo = 4u * uint32_t(j), c = 4u * uint32_t(r * (L / R) + (r < R / 4 ? N / 2 : N / 2 - L));
+    const float dx = buf_load<float>(dp, jo, c);
+    return make_float2(dx * d0 * buf_load<float>(f, jo, c), dx * d1 * buf_load<float>(f, jo, c + 4u * N));
   });
   // split the two real transforms: A = (Z_q + conj Z_-q)/2, B = (Z_q - conj Z_-q)/(2i)
-  NR_G float4* __restrict__ out = (NR_G float4*)d.T;
+  const Rsrc out = buf(d.T, t_bytes<L>());
+  static_assert(T % 16 == 0, "whole swizzle blocks per step");
+  const uint32_t o0 = 16u * t4(tid, iy0 >> 1, N);
   NR_STRIDED(q, L / 2 + 1, T) {
-    const float2 z1 = s[q], z2 = s[q == 0 ? 0 : L - q];
+    const float2 z1 = s.at(tid, q_it * T), z2 = q_it == 0 ? s[q == 0 ? 0 : L - q] : s.at(L - tid, -q_it * T);
     float4 o;
     o.x = 0.5f * (z1.x + z2.x);
     o.y = 0.5f * (z1.y - z2.y);
     o.z = 0.5f * (z1.y + z2.y);
     o.w = 0.5f * (z2.x - z1.x);
-    out[t4(q, iy0 >> 1, N)] = o;
+    buf_store(out, o0, uint32_t(q_it * (T / 4) * (N / 2) * 64), o);
   }
   __syncthreads();
 }
@@ -316,16 +391,19 @@ template <int L, int T, class LA>
 __device__ __forceinline__ void fwd_cols_unit(const LA& a, const WorkItem wi, float2* sbuf, const int tid) {
   const Lds s{sbuf};
   const int halo = a.halo, colpad = a.colpad;
-  const DSlice d = load_desc(a.descs + wi.slice);
+  const DSlice d = load_desc(a.descs, wi.slice);
   constexpr int N = L / 2;   // G = 2N
   const int cols = d.cols;
-  const int qx = wi.unit;
+  const int qx = __builtin_amdgcn_readfirstlane(wi.unit);
   // y = iy - N/2 sits at index y mod L; row iy of column qx is half iy & 1
   // of the tile entry t4(qx, iy / 2)
-  const NR_G float2* __restrict__ T2 = (const NR_G float2*)d.T;
-  fft_first_pass_from<L, T, false, true>(s, tid, [&](int n) {
-    const int iy = n < N / 2 ? n + N / 2 : n - (L - N / 2);
-    return T2[2 * t4(qx, iy >> 1, N) + (iy & 1)];
+  const Rsrc Tq = buf((const NR_G float4*)d.T + t4(qx, 0, N), 32u * N);
+  fft_first_pass_from<L, T, false, true>(s, tid, [&](int j, int r) {
+    // row iy = j + c, c even: 64 bytes per two rows
+    constexpr int R = radix_of(L, 0);
+    const int c = r * (L / R) + (r < R / 4 ? N / 2 : N / 2 - L);
+    static_assert((L / R) % 2 == 0 && N % 4 == 0, "row pairs");
+    return buf_load<float2>(Tq, uint32_t(j >> 1) * 64u + uint32_t(j & 1) * 8u, uint32_t(c) * 32u);
   });
   NR_G float2* ext = d.ext;
   NR_G float2* row = ext + size_t(qx + halo) * cols;
@@ -388,8 +466,8 @@ __global__ __launch_bounds__(fft_threads(L)) void k_fwd_cols(LaunchArgs a) {
   // the adjoint columns slower (21.7 -> 22.3, 24.4 -> 28.6, 34.0 -> 43.4 us).
   if (a.pair_units) {
     const int p0 = 16 * (int(blockIdx.x) >> 3) + (int(blockIdx.x) & 7), p1 = p0 + 8;
-    const WorkItem w0 = p0 < a.n_work ? a.work[p0] : WorkItem{-1, 0};
-    const WorkItem w1 = p1 < a.n_work ? a.work[p1] : WorkItem{-1, 0};
+    const WorkItem w0 = work_entry(a, p0);
+    const WorkItem w1 = work_entry(a, p1);
     if (w0.slice >= 0) fwd_cols_unit<L, fft_threads(L)>(a, w0, sbuf, int(threadIdx.x));
     __syncthreads();
     if (w1.slice >= 0) fwd_cols_unit<L, fft_threads(L)>(a, w1, sbuf, int(threadIdx.x));
@@ -459,7 +537,7 @@ template <int L, int W, int T, class LA, class KB>
 __device__ __forceinline__ void fwd_interp_unit(const LA& a, const KB& kb, const WorkItem wi, float2* sbuf, const int tid) {
   const Lds s{sbuf};
   const float inv = 1.0f / float(L);
-  const DSlice d = load_desc(a.descs + wi.slice);
+  const DSlice d = load_desc(a.descs, wi.slice);
   const int a0 = 2 * wi.unit, a1 = a0 + 1;
   const bool has1 = a1 < d.na;
   // both half-lines per iteration (two independent gathers in flight), packed
@@ -493,8 +571,8 @@ template <int T, int PER, class LA>
 __device__ __forceinline__ void interp_fetch_points(const LA& a, const WorkItem wi, DSlice& d, SpreadItem& it,
                                                     int (&codes)[PER], double (&gx)[PER], double (&gy)[PER],
                                                     int (&fl)[PER], const int tid) {
-  d = load_desc(a.descs + wi.slice);
-  it = d.iitems[wi.unit];
+  d = load_desc(a.descs, wi.slice);
+  it = load_item(d.iitems, wi.unit);
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int e = tid + k * T;
@@ -630,8 +708,8 @@ __global__ __launch_bounds__(256) void k_interp_tiles(LaunchArgs a, KBArgs kb) {
   __shared__ float2 reg[InterpLds<W>::RH * InterpLds<W>::RS];
   const int tid = int(threadIdx.x);
   const int b0 = int(blockIdx.x), b1 = a.n_work - 1 - b0;
-  const WorkItem w0 = b0 < a.n_work ? a.work[b0] : WorkItem{-1, 0};
-  const WorkItem w1 = b1 > b0 ? a.work[b1] : WorkItem{-1, 0};
+  const WorkItem w0 = work_entry(a, b0);
+  const WorkItem w1 = b1 > b0 ? work_entry(a, b1) : WorkItem{-1, 0};
   DSlice d0, d1;
   SpreadItem i0, i1;
   int c0[PER], f0[PER], c1[PER], f1[PER];
@@ -661,7 +739,7 @@ template <int L, int T, class LA>
 __device__ __forceinline__ void fwd_radial_unit(const LA& a, const WorkItem wi, float2* sbuf, const int tid) {
   const Lds s{sbuf};
   constexpr int H = L / 2 + 1;
-  const DSlice d = load_desc(a.descs + wi.slice);
+  const DSlice d = load_desc(a.descs, wi.slice);
   const int a0 = 2 * wi.unit, a1 = a0 + 1;
   const bool has1 = a1 < d.na;
   const NR_G float2* __restrict__ x0 = d.yh + size_t(a0) * H;
@@ -717,7 +795,7 @@ template <int L, int T, class LA>
 __device__ __forceinline__ void adj_radial_unit(const LA& a, const WorkItem wi, float2* sbuf, const int tid) {
   const Lds s{sbuf};
 
-  const DSlice d = load_desc(a.descs + wi.slice);
+  const DSlice d = load_desc(a.descs, wi.slice);
   const int a0 = 2 * wi.unit, a1 = a0 + 1;
   const bool has1 = a1 < d.na;
   const float* __restrict__ y0 = a.sino_in + d.sino_off + size_t(a0) * L;
@@ -767,7 +845,7 @@ __global__ void k_fill_zero(float4* p, size_t n4) {
 template <int TW, int TH, class LA>
 __device__ __forceinline__ void spread_zero_unit(const LA& a, const WorkItem wi, const int tid) {
 
-  const DSlice d = load_desc(a.descs + wi.slice);
+  const DSlice d = load_desc(a.descs, wi.slice);
   const int t = d.zero_tiles[wi.unit];
   const int r0 = (t / d.tiles_x) * TH, c0 = (t % d.tiles_x) * TW;
   NR_G float2* ext = d.ext;
@@ -816,8 +894,8 @@ __global__ __launch_bounds__(256) void k_spread_zero(LaunchArgs a) {
 template <int T, int PER, class LA>
 __device__ __forceinline__ void spread_fetch_codes(const LA& a, const WorkItem wi, DSlice& d, SpreadItem& it,
                                                    int (&code)[PER], const int tid) {
-  d = load_desc(a.descs + wi.slice);
-  it = d.items[wi.unit];
+  d = load_desc(a.descs, wi.slice);
+  it = load_item(d.items, wi.unit);
   const int count = it.end - it.begin;   // at most kMaxChunk
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
@@ -1018,8 +1096,8 @@ __global__ __launch_bounds__(kSpreadThreads) void k_spread_tiles(LaunchArgs a, K
   __shared__ int nonfinite;
   const int tid = int(threadIdx.x);
   const int b0 = int(blockIdx.x), b1 = a.n_work - 1 - b0;
-  const WorkItem w0 = b0 < a.n_work ? a.work[b0] : WorkItem{-1, 0};
-  const WorkItem w1 = b1 > b0 ? a.work[b1] : WorkItem{-1, 0};
+  const WorkItem w0 = work_entry(a, b0);
+  const WorkItem w1 = b1 > b0 ? work_entry(a, b1) : WorkItem{-1, 0};
   constexpr int PER = kMaxChunk / T;
   DSlice d0, d1;
   SpreadItem i0, i1;
@@ -1038,7 +1116,7 @@ __global__ __launch_bounds__(kSpreadThreads) void k_spread_tiles(LaunchArgs a, K
 template <int W>
 __global__ __launch_bounds__(256) void k_spread_atomic(const SliceDesc* descs, int slice, int halo, int colpad,
                                                        KBArgs kb) {
-  const DSlice d = load_desc(descs + slice);
+  const DSlice d = load_desc(descs, slice);
   const int pid = blockIdx.x * 256 + threadIdx.x;
   if (pid >= d.na * d.H) return;
   const int ang = pid / d.H, j = pid - ang * d.H;
@@ -1069,12 +1147,26 @@ __device__ __forceinline__ float2 load_folded(const NR_G float2* row, int colpad
   return v;
 }
 
-template <int L, int T, class LA>
+// The cells |q_y| <= lim of a row, and input r of first-pass butterfly j from
+// them: zero outside (the offset then lies past the descriptor's end, a
+// negative one as a large unsigned number).
+template <int L>
+__device__ __forceinline__ Rsrc disc_cells(const NR_G float2* row, int colpad, int lim) {
+  return buf(row + colpad + L / 2 - max(lim, 0), 8u * uint32_t(max(2 * lim + 1, 0)));
+}
+template <int L>
+__device__ __forceinline__ float2 disc_cell(Rsrc disc, int lim, int j, int r) {
+  constexpr int R = radix_of(L, 0);
+  static_assert(R % 2 == 0, "q_y changes sign between two inputs of a butterfly");
+  const int qy = j + r * (L / R) - (r < R / 2 ? 0 : L);
+  return buf_load<float2>(disc, 8u * uint32_t(qy + lim), 0u);
+}
+
+template <int L, int T, bool SPLIT, class LA>
 __device__ __forceinline__ void adj_cols_unit(const LA& a, const WorkItem wi, float2* sbuf, const int tid) {
-  const Lds s{sbuf};
   const int halo = a.halo, colpad = a.colpad;
-  const DSlice d = load_desc(a.descs + wi.slice);
-  const int qx = wi.unit;
+  const DSlice d = load_desc(a.descs, wi.slice);
+  const int qx = __builtin_amdgcn_readfirstlane(wi.unit);
   const int cols = d.cols;
   constexpr int N = L / 2;   // G = 2N
   const NR_G float2* ext = d.ext;
@@ -1091,8 +1183,10 @@ __device__ __forceinline__ void adj_cols_unit(const LA& a, const WorkItem wi, fl
   // column whose disc stops short of them, and that has no mirror rows (all
   // but a few), reads each cell once.
   const int lim = r2 < 0 ? -1 : int(sqrtf(float(r2)));
+  Regs<L, T, 0> in;
   if (m1 || m2 || lim >= L / 2 - colpad) {
-    fft_first_pass_from<L, T, true, false>(s, tid, [&](int n) {
+    first_inputs<L, T>(in, tid, [&](int j, int r) {
+      const int n = j + r * (L / radix_of(L, 0));
       const int qy = n < L / 2 ? n : n - L;
       if (qy * qy > r2) return make_float2(0.f, 0.f);
       float2 v = load_folded<L>(row, colpad, n);
@@ -1102,72 +1196,85 @@ __device__ __forceinline__ void adj_cols_unit(const LA& a, const WorkItem wi, fl
       return v;
     });
   } else {
-    const NR_G float2* __restrict__ mid = row + colpad + L / 2;   // the cell of q_y = 0
-    fft_first_pass_from<L, T, true, false>(s, tid, [&](int n) {
-      const int qy = n < L / 2 ? n : n - L;
-      if (qy * qy > r2) return make_float2(0.f, 0.f);
-      const float2 v = mid[qy];
-      return v;
-    });
+    const Rsrc disc = disc_cells<L>(row, colpad, lim);
+    first_inputs<L, T>(in, tid, [&](int j, int r) { return disc_cell<L>(disc, lim, j, r); });
   }
   // only y = iy - N/2 in [-N/2, N/2) is kept: natural indices [0, N/2) and
   // [L - N/2, L); row iy of column qx is half iy & 1 of tile entry t4(qx, iy / 2)
-  NR_G float2* __restrict__ T2 = (NR_G float2*)d.T;
-  fft_lds_store_out<L, T, true, 1>(s, d.tw_G, tid, [&](int n, float2 v) {
-    const int iy = n < N / 2 ? n + N / 2 : n - (L - N / 2);
-    T2[2 * t4(qx, iy >> 1, N) + (iy & 1)] = v;
+  const Rsrc Tq = buf((const NR_G float4*)d.T + t4(qx, 0, N), 32u * N);
+  fft_store_out<L, T, true, SPLIT>(sbuf, d.tw_G, tid, in, [&](int j, int r, float2 v) {
+    constexpr int Ns = L / radix_of(L, num_passes(L) - 1);
+    const int c = r * Ns + (r * Ns < L / 2 ? N / 2 : N / 2 - L);   // row iy = j + c, c even
+    static_assert(Ns % 2 == 0, "row pairs");
+    // (c < 0, where a radix splits the kept outputs unevenly, goes into the lane's offset)
+    const int jl = c < 0 ? j + c : j;
+    buf_store(Tq, uint32_t(jl >> 1) * 64u + uint32_t(jl & 1) * 8u, uint32_t(max(c, 0)) * 32u, v);
   });
   __syncthreads();
 }
 
+// wavefronts per SIMD the adjoint transforms are compiled for: with the split
+// exchange six (80 VGPRs; seven spill a few at L = 5120 and ran slower)
+constexpr int store_out_waves(int L) { return split_exchange_length(L) ? 6 : 1; }
+
 template <int L>
-__global__ __launch_bounds__(fft_threads(L)) void k_adj_cols(LaunchArgs a) {
-  __shared__ float2 sbuf[lds_elems<L>()];
-  NR_FOR_EACH_UNIT(a, wi) adj_cols_unit<L, fft_threads(L)>(a, wi, sbuf, int(threadIdx.x));
+__global__ __launch_bounds__(fft_threads(L)) __attribute__((amdgpu_waves_per_eu(store_out_waves(L)))) void k_adj_cols(
+    LaunchArgs a) {
+  constexpr bool SPLIT = split_exchange_length(L);
+  __shared__ float2 sbuf[store_out_lds_elems<L, SPLIT>()];
+  NR_FOR_EACH_UNIT(a, wi) adj_cols_unit<L, fft_threads(L), SPLIT>(a, wi, sbuf, int(threadIdx.x));
 }
 
 // ---------------------------------------------------------------------------
 // A4: transpose of the row R2C: a'(x) = Re sum_{q=0}^{G/2} T'[q] e^{2 pi i q x/G}
 // ---------------------------------------------------------------------------
 
-template <int L, int T, class LA>
+template <int L, int T, bool SPLIT, class LA>
 __device__ __forceinline__ void adj_rows_unit(const LA& a, const WorkItem wi, float2* sbuf, const int tid) {
-  const Lds s{sbuf};
-
-  const DSlice d = load_desc(a.descs + wi.slice);
+  const DSlice d = load_desc(a.descs, wi.slice);
   constexpr int N = L / 2;   // G = 2N
-  const int iy0 = 2 * wi.unit;
-  const NR_G float4* __restrict__ in = (const NR_G float4*)d.T;
+  const int iy0 = 2 * __builtin_amdgcn_readfirstlane(wi.unit);
+  const Rsrc in = buf(d.T, t_bytes<L>());
   // Hermitian completion with doubled real parts at q = 0 and G/2, two rows
   // packed: index n <= L/2 takes entry q = n as X + iY, index L - q the
   // conjugate-symmetric combination of the same entry
-  fft_first_pass_from<L, T, true, false>(s, tid, [&](int n) {
-    const int q = n <= L / 2 ? n : L - n;
-    const float4 t = in[t4(q, iy0 >> 1, N)];
+  Regs<L, T, 0> cells;
+  first_inputs<L, T>(cells, tid, [&](int j, int r) {
+    constexpr int R = radix_of(L, 0), NB = L / R;
+    static_assert(NB % 4 == 0 && R % 2 == 0, "whole tiles of T per input");
+    // r < R/2: q = n = j + r NB; else q = L - n = (NB - j) + (R - 1 - r) NB
+    const bool low = r < R / 2;
+    const int n = j + r * NB, q = low ? n : L - n;
+    const float4 t = buf_load<float4>(in, 16u * t4(low ? j : NB - j, iy0 >> 1, N),
+                                      uint32_t((low ? r : R - 1 - r) * (NB / 4)) * uint32_t(N / 2) * 64u);
     float2 X = make_float2(t.x, t.y), Y = make_float2(t.z, t.w);
     if (q == 0 || q == L / 2) {
       X = make_float2(2.f * X.x, 0.f);
       Y = make_float2(2.f * Y.x, 0.f);
     }
-    return n <= L / 2 ? make_float2(X.x - Y.y, X.y + Y.x) : make_float2(X.x + Y.y, Y.x - X.y);
+    return low || n == L / 2 ? make_float2(X.x - Y.y, X.y + Y.x) : make_float2(X.x + Y.y, Y.x - X.y);
   });
   const float d0 = 0.5f * d.deapod[iy0], d1 = 0.5f * d.deapod[iy0 + 1];
-  float* __restrict__ g0 = a.vol_out + d.vol_off + size_t(iy0) * N;
-  const NR_G float* __restrict__ dp = d.deapod;
+  const Rsrc g = buf((NR_G float*)a.vol_out + d.vol_off + size_t(iy0) * N, 8u * N);
+  const Rsrc dp = buf(d.deapod, 4u * N);
   // x = ix - N/2 in [-N/2, N/2) is kept: natural indices [0, N/2) and [L - N/2, L)
-  fft_lds_store_out<L, T, true, 1>(s, d.tw_G, tid, [&](int n, float2 z) {
-    const int ix = n < N / 2 ? n + N / 2 : n - (L - N / 2);
-    const float dx = dp[ix];
-    g0[ix] = dx * d0 * z.x;
-    g0[N + ix] = dx * d1 * z.y;
+  fft_store_out<L, T, true, SPLIT>(sbuf, d.tw_G, tid, cells, [&](int j, int r, float2 z) {
+    constexpr int Ns = L / radix_of(L, num_passes(L) - 1);
+    const int ix0 = r * Ns + (r * Ns < L / 2 ? N / 2 : N / 2 - L);   // ix = j + ix0
+    const uint32_t jo = 4u * uint32_t(ix0 < 0 ? j + ix0 : j), c = 4u * uint32_t(max(ix0, 0));
+    const float dx = buf_load<float>(dp, jo, c);
+    buf_store(g, jo, c, dx * d0 * z.x);
+    buf_store(g, jo, c + 4u * N, dx * d1 * z.y);
   });
   __syncthreads();
 }
 
 template <int L>
-__global__ __launch_bounds__(fft_threads(L)) void k_adj_rows(LaunchArgs a) {
-  __shared__ float2 sbuf[lds_elems<L>()];
-  NR_FOR_EACH_UNIT(a, wi) adj_rows_unit<L, fft_threads(L)>(a, wi, sbuf, int(threadIdx.x));
+__global__ __launch_bounds__(fft_threads(L)) __attribute__((amdgpu_waves_per_eu(store_out_waves(L)))) void k_adj_rows(
+    LaunchArgs a) {
+  constexpr bool SPLIT = split_exchange_length(L);
+  __shared__ float2 sbuf[store_out_lds_elems<L, SPLIT>()];
+  NR_FOR_EACH_UNIT(a, wi) adj_rows_unit<L, fft_threads(L), SPLIT>(a, wi, sbuf, int(threadIdx.x));
 }
 
 // ---------------------------------------------------------------------------
@@ -1186,13 +1293,6 @@ __global__ __launch_bounds__(fft_threads(L)) void k_adj_rows(LaunchArgs a) {
 // workgroup stops taking tickets, so every workgroup exits.
 
 constexpr int kPersistThreads = 256;
-
-// kernel-argument (constant) address space: loads through it are scalar
-#ifdef __HIP_DEVICE_COMPILE__
-#define NR_C __attribute__((address_space(4)))
-#else
-#define NR_C
-#endif
 
 template <int W>
 struct PersistLds {
@@ -1257,14 +1357,14 @@ __device__ __forceinline__ void persist_unit(const LA& a, const KB& kb, int stag
     }
     case StageKind::AdjCols:
       switch (L) {
-#define NR_CASE(l) case l: adj_cols_unit<l, T>(a, wi, f2, tid); return;
+#define NR_CASE(l) case l: adj_cols_unit<l, T, false>(a, wi, f2, tid); return;
         NR_PERSIST_LENGTHS(NR_CASE)
 #undef NR_CASE
       }
       return;
     case StageKind::AdjRows:
       switch (L) {
-#define NR_CASE(l) case l: adj_rows_unit<l, T>(a, wi, f2, tid); return;
+#define NR_CASE(l) case l: adj_rows_unit<l, T, false>(a, wi, f2, tid); return;
         NR_PERSIST_LENGTHS(NR_CASE)
 #undef NR_CASE
       }

@@ -24,7 +24,7 @@
 // on the caller's stream, read back (and synchronised) on request.
 enum {
   kStageFwdRows = 0, kStageFwdCols, kStageFwdInterp, kStageAdjRadial, kStageSpread, kStageAdjCols,
-  kStageAdjRows, kStageResidual, kStagePrior, kStageUpdate, kStageSpreadClear, kStageCount
+  kStageAdjRows, kStageResidual, kStagePrior, kStageUpdate, kStageSpreadShared, kStageCount
 };
 
 struct StageEvents {
@@ -181,7 +181,7 @@ int stage_event_id(nr::Stage s) {
     case nr::Stage::FwdInterp:
     case nr::Stage::FwdRadial: return kStageFwdInterp;
     case nr::Stage::AdjRadial: return kStageAdjRadial;
-    case nr::Stage::SpreadZero: return kStageSpreadClear;
+    case nr::Stage::SpreadShared: return kStageSpreadShared;
     case nr::Stage::Spread: return kStageSpread;
     case nr::Stage::AdjCols: return kStageAdjCols;
     case nr::Stage::AdjRows: return kStageAdjRows;
@@ -303,22 +303,29 @@ nr_status run_batches(nr_plan* plan, bool fwd, const float* b, bool adj, const f
     // batch has issued 1/nl of its stages, so concurrent lanes run different
     // kinds of stage (transforms, gathers, scatters) rather than the same one.
     const bool first = int(bi) < nl;
+    // (The stage that adds up shared tiles belongs to the spreading before it:
+    // the pair counts as two stages that start together.)
     const size_t skew_at = nl > 1 ? std::max<size_t>(1, seq.size() / size_t(nl)) : 0;
+    size_t started = 0;
+    bool skewed = false;
     if (nl > 1 && first && bt.lane > 0) {
       const hipError_t e = hipStreamWaitEvent(bs, plan->lane_skew[size_t(bt.lane - 1)], 0);
       if (e != hipSuccess) return hip_fail(e, where);
     }
     for (size_t si = 0; si < seq.size(); ++si) {
-      if (nl > 1 && first && si == skew_at && bt.lane + 1 < nl) {
+      const bool pair = si + 1 < seq.size() && seq[si + 1]->stage == nr::Stage::SpreadShared;
+      if (nl > 1 && first && !skewed && started + (pair ? 1 : 0) >= skew_at && bt.lane + 1 < nl) {
+        skewed = true;
         const hipError_t e = hipEventRecord(plan->lane_skew[size_t(bt.lane)], bs);
         if (e != hipSuccess) return hip_fail(e, where);
       }
       const nr::StageLaunch& sl = *seq[si];
-      const bool spread = sl.stage == nr::Stage::Spread || sl.stage == nr::Stage::SpreadZero;
+      started += pair ? 2 : (sl.stage == nr::Stage::SpreadShared ? 0 : 1);
+      const bool spread = sl.stage == nr::Stage::Spread || sl.stage == nr::Stage::SpreadShared;
       hipError_t e = hipSuccess;
       if (spread && p.tune.spread_mode == 1) {
         // reference spreading, one slice at a time
-        if (sl.stage == nr::Stage::SpreadZero) continue;
+        if (sl.stage == nr::Stage::SpreadShared) continue;
         for (int s : bt.slices) {
           e = timed(plan, kStageSpread, bs, [&] {
             return nrk::launch_spread_reference(a.descs, s, plan->host_descs[size_t(s)], p.halo, p.colpad, kb,
@@ -460,7 +467,7 @@ hipError_t upload_tables(const nr::Plan& p, char* base, const std::vector<SliceD
     if ((e = up(g.off_flip, g.flip.data(), g.flip.size() * sizeof(int32_t)))) return e;
     if ((e = up(g.off_pts, g.pts.data(), g.pts.size() * sizeof(int32_t)))) return e;
     if ((e = up(g.off_items, g.items.data(), g.items.size() * sizeof(SpreadItem)))) return e;
-    if ((e = up(g.off_zero, g.zero_tiles.data(), g.zero_tiles.size() * sizeof(int32_t)))) return e;
+    if ((e = up(g.off_shared, g.shared.data(), g.shared.size() * sizeof(SharedTile)))) return e;
     if ((e = up(g.off_ipts, g.ipts.data(), g.ipts.size() * sizeof(int32_t)))) return e;
     if ((e = up(g.off_iitems, g.iitems.data(), g.iitems.size() * sizeof(SpreadItem)))) return e;
   }

@@ -7,16 +7,25 @@
 struct SpreadItem {
   int32_t tile;         // tile index (row-major over tiles)
   int32_t begin, end;   // range in the geometry's point-index list
-  int32_t flags;        // bit 0: tile shared by several items (accumulate with atomics)
+  int32_t flags;        // bit 0: tile shared by several items (the item's sums go to its part)
                         // bit 1: this item also spreads the k = 0 point of every angle
   int32_t bound;        // most points of this item that touch any one cell of the tile
+  int32_t part;         // index of the item's part buffer (shared tiles only)
 };
-enum { kItemAtomic = 1, kItemDC = 2 };
+enum { kItemPart = 1, kItemDC = 2 };
+
+// A tile that several spreading items share: their sums lie in parts
+// [first, first + count), and are added into the tile afterwards.
+struct SharedTile {
+  int32_t tile, first, count;
+};
+// units of work a shared tile's parts are added up in (each a fourth of its rows)
+constexpr int kSharedTileUnits = 4;
 
 // Interpolation tiles: a point belongs to the tile holding its first tap; the
 // kernel stages the tile plus W + 1 cells (the footprint and a one-cell
 // margin on each side) of the grid in LDS.  Interpolation items reuse
-// SpreadItem with flags = bound = 0.
+// SpreadItem with flags = bound = part = 0.
 constexpr int kInterpTileW = 64, kInterpTileH = 32;
 
 // Most points per spreading or interpolation work item (the kernels keep an
@@ -26,7 +35,7 @@ constexpr int kMaxChunk = 1024;
 // One slice as the kernels see it (device resident, filled at bind time).
 // Complex buffers are float pairs.
 struct SliceDesc {
-  int32_t N, Nt, na, G, H, rows, cols, tiles_x, n_items, n_zero, slot, itiles_x;
+  int32_t N, Nt, na, G, H, rows, cols, tiles_x, n_items, slot, itiles_x;
   int32_t rdisc;                  // cells of ext farther than rdisc from the origin are never read
   int32_t jbits;                  // point codes in pts/ipts: (angle << jbits) | radial index
   int64_t vol_off, sino_off;      // element offsets into the caller's buffers
@@ -41,7 +50,8 @@ struct SliceDesc {
   float* yh;                      // [na][H] complex
   const int32_t* pts;             // spreading point lists (tile-major)
   const SpreadItem* items;        // spreading work items of this slice's geometry
-  const int32_t* zero_tiles;      // tiles written by several items
+  const SharedTile* shared;       // tiles that several items share
+  float* parts;                   // [part][tile_h][tile_w] complex: the sums of their items
   const int32_t* ipts;            // interpolation point lists (tile-major, every point once)
   const SpreadItem* iitems;       // interpolation work items (tile, point range)
 };

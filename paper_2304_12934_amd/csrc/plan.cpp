@@ -159,6 +159,23 @@ int disc_radius(const Plan& plan, const Geom& g) {
   return g.G / 2 + (plan.kb.W + 1) / 2 + 2;
 }
 
+// With few points in the whole plan, items of kMaxChunk leave most of the GPU
+// idle and each item runs its rounds of 256 points one after the other, so the
+// items shrink (to one round at least) until the plan has about `items` of
+// them.  Interpolation: 1024 items (a split tile is only staged again): 361
+// angles of one 2048^2 slice 29.4 -> 26.7 us with the radial pass, 181 angles
+// of one 128^2 slice 16.2 -> 13.1.  Spreading: 64, since the items of a split
+// tile add a write and a read of its cells each: 181 angles of a 128^2 slice
+// 16.5 -> 10.5 us, 180 of a 256^2 slice 16.8 -> 10.5; with 256 items sixteen
+// 512^2 slices and four 1024^2 ones run the same, one 1280^2 slice slower.
+int item_points(const Plan& plan, int64_t items) {
+  int64_t points = 0;
+  for (int gi : plan.slice_geom) points += int64_t(plan.geoms[size_t(gi)].key.n_angles) * plan.geoms[size_t(gi)].H;
+  int64_t c = kMaxChunk;
+  while (c > 256 && points < items * c) c /= 2;
+  return int(std::min<int64_t>(plan.tune.chunk, c));
+}
+
 void build_spread_bins(const Plan& plan, Geom& g) {
   const int W = plan.kb.W;
   const int na = g.key.n_angles;
@@ -194,16 +211,17 @@ void build_spread_bins(const Plan& plan, Geom& g) {
   for (int a = 0; a < na; ++a)
     for (int j = 1; j < g.H; ++j)
       for_tiles(a, j, [&](int t) { g.pts[size_t(fill[t]++)] = (a << g.jbits) | j; });
-  // work items: at most `chunk` points each; tiles cut into several items
-  // accumulate with atomics into a grid region cleared beforehand
-  const int chunk = plan.tune.chunk;
+  // work items: at most `chunk` points each; the items of a tile cut into
+  // several write their sums to parts, which are added up afterwards
+  const int chunk = item_points(plan, 64);
   // the k = 0 point of every angle sits at the origin: it is summed over the
   // angles once and spread by the first item of each tile its footprint touches
   const int d0 = int(std::ceil(-halfW));
   const int dr0 = d0 + plan.halo, dr1 = d0 + plan.halo + W - 1;
   const int dc0 = d0 + g.G / 2 + plan.colpad, dc1 = dc0 + W - 1;
   g.items.clear();
-  g.zero_tiles.clear();
+  g.shared.clear();
+  g.n_parts = 0;
   // The adjoint column transform reads only cells whose natural frequency
   // (mirror rows folded back, periodic columns wrapped) lies within rdisc of
   // the origin.  A tile without points and without such a cell is neither
@@ -228,7 +246,7 @@ void build_spread_bins(const Plan& plan, Geom& g) {
     const int n_items = std::max(1, (e - b + chunk - 1) / chunk);
     const bool has_dc = ty * g.tile_h <= dr1 && (ty + 1) * g.tile_h > dr0 &&
                         tx * g.tile_w <= dc1 && (tx + 1) * g.tile_w > dc0;
-    if (n_items > 1) g.zero_tiles.push_back(t);
+    if (n_items > 1) g.shared.push_back({t, g.n_parts, n_items});
     for (int k = 0; k < n_items; ++k) {
       const int ib = b + int((int64_t(e - b) * k) / n_items);
       const int ie = b + int((int64_t(e - b) * (k + 1)) / n_items);
@@ -247,8 +265,8 @@ void build_spread_bins(const Plan& plan, Geom& g) {
       }
       // (the origin's k = 0 sum is added in float32 at write-out, outside the
       // fixed-point sums)
-      const int flags = (n_items > 1 ? kItemAtomic : 0) | (has_dc && k == 0 ? kItemDC : 0);
-      g.items.push_back({t, ib, ie, flags, cmax + 1});
+      const int flags = (n_items > 1 ? kItemPart : 0) | (has_dc && k == 0 ? kItemDC : 0);
+      g.items.push_back({t, ib, ie, flags, cmax + 1, n_items > 1 ? g.n_parts++ : 0});
     }
   }
   // heaviest items first so the long ones start early
@@ -282,7 +300,7 @@ void build_interp_bins(const Plan& plan, Geom& g) {
   // angle-major within a tile: neighbouring threads take neighbouring points of one line
   for (int a = 0; a < na; ++a)
     for (int j = 0; j < g.H; ++j) g.ipts[size_t(fill[size_t(tile_of(a, j))]++)] = (a << g.jbits) | j;
-  const int chunk = plan.tune.chunk;
+  const int chunk = item_points(plan, 1024);
   g.iitems.clear();
   for (int t = 0; t < ntiles; ++t) {
     const int b = start[size_t(t)], e = start[size_t(t) + 1];
@@ -291,12 +309,9 @@ void build_interp_bins(const Plan& plan, Geom& g) {
     for (int k = 0; k < n_items; ++k) {
       const int ib = b + int((int64_t(e - b) * k) / n_items);
       const int ie = b + int((int64_t(e - b) * (k + 1)) / n_items);
-      g.iitems.push_back({t, ib, ie, 0, 0});
+      g.iitems.push_back({t, ib, ie, 0, 0, 0});   // in tile order: neighbours in the grid are neighbours in the list
     }
   }
-  std::stable_sort(g.iitems.begin(), g.iitems.end(), [](const SpreadItem& x, const SpreadItem& y) {
-    return (x.end - x.begin) > (y.end - y.begin);
-  });
 }
 
 // ---------------------------------------------------------------------------
@@ -475,6 +490,41 @@ void append_units(std::vector<WorkItem>& out, const std::vector<WorkItem>& logic
   }
 }
 
+// The same for units of unequal cost whose neighbours in the list share data:
+// each XCD gets a contiguous run of about an eighth of the summed cost (the
+// shorter runs padded).
+template <class Dear>
+void append_units_by_cost(std::vector<WorkItem>& out, const std::vector<WorkItem>& logical, const std::vector<int>& cost,
+                          Dear&& dear) {
+  int64_t total = 0, before = 0;
+  for (int c : cost) total += c;
+  std::vector<WorkItem> run[8];
+  for (size_t i = 0; i < logical.size(); ++i) {
+    run[std::min<int64_t>(7, 8 * before / std::max<int64_t>(1, total))].push_back(logical[i]);
+    before += cost[i];
+  }
+  // a run's dear units first, the rest in list order
+  for (auto& r : run) std::stable_partition(r.begin(), r.end(), dear);
+  size_t per = 0;
+  for (const auto& r : run) per = std::max(per, r.size());
+  for (size_t k = 0; k < per; ++k)
+    for (const auto& r : run) out.push_back(k < r.size() ? r[k] : WorkItem{-1, 0});
+}
+
+// Scratch of one slice: T (its q rows rounded up to a multiple of 4), ext, yh
+// and the parts of its shared tiles, each 256-byte aligned (offsets in bytes).
+struct SliceScratch {
+  size_t ext, yh, parts, bytes;
+};
+SliceScratch slice_scratch(const Geom& g) {
+  SliceScratch o{};
+  o.ext = align_up(size_t((g.G / 2 + 4) / 4 * 4) * g.key.n * sizeof(f2), 256);
+  o.yh = align_up(o.ext + size_t(g.rows) * g.cols * sizeof(f2), 256);
+  o.parts = align_up(o.yh + size_t(g.key.n_angles) * g.H * sizeof(f2), 256);
+  o.bytes = align_up(o.parts + size_t(g.n_parts) * g.tile_w * g.tile_h * sizeof(f2), 256);
+  return o;
+}
+
 }  // namespace
 
 nr_status layout_plan(Plan& plan, std::string& err) {
@@ -510,14 +560,6 @@ nr_status layout_plan(Plan& plan, std::string& err) {
   }
 
   const int ns = int(plan.slices.size());
-  // per-slice scratch: T (its q rows rounded up to a multiple of 4), ext and
-  // yh, each 256-byte aligned
-  auto scratch_bytes = [&](const Geom& g, size_t& t_off, size_t& ext_off, size_t& yh_off) {
-    t_off = 0;
-    ext_off = align_up(size_t((g.G / 2 + 4) / 4 * 4) * g.key.n * sizeof(f2), 256);
-    yh_off = align_up(ext_off + size_t(g.rows) * g.cols * sizeof(f2), 256);
-    return align_up(yh_off + size_t(g.key.n_angles) * g.H * sizeof(f2), 256);
-  };
   if (tu.batch < 0 || tu.batch_mb < 0) {
     err = "batch and batch_mb must be >= 0";
     return NR_INVALID_ARG;
@@ -539,8 +581,7 @@ nr_status layout_plan(Plan& plan, std::string& err) {
     size_t used = 0;
     for (int s = b0; s < ns; ++s) {
       const Geom& g = plan.geoms[size_t(plan.slice_geom[size_t(s)])];
-      size_t t_off, e_off, y_off;
-      const size_t need = scratch_bytes(g, t_off, e_off, y_off);
+      const size_t need = slice_scratch(g).bytes;
       if (!bt.slices.empty() && (used + need > budget || (tu.batch > 0 && int(bt.slices.size()) >= tu.batch)))
         break;
       bt.slices.push_back(s);
@@ -606,24 +647,46 @@ nr_status layout_plan(Plan& plan, std::string& err) {
       return std::vector<StageLaunch>{sl};
     };
     if (tu.interp_mode == 0) {
-      for (const StageLaunch& sl : heaviest_first(Stage::FwdInterp, [](const Geom& g) -> const std::vector<SpreadItem>& {
-             return g.iitems;
-           }))
-        bt.fwd.push_back(sl);
+      // interpolation items in grid order, a contiguous run per XCD: a staged tile
+      // shares a third of its cells with its neighbours, which then come from
+      // the XCD's L2 (with the radial pass, us per slice against heaviest-first:
+      // 2560^2 33.2 -> 32.0, 2048^2 18.3 -> 17.0, 1280^2 7.65 -> 7.1).  An item
+      // costs its points and its staging, taken as 256 points: a lone 2560^2
+      // slice of 1024 angles, whose run near the origin is dense, ran 55.1 us
+      // with 1024, 50.8 with 512 and 49.1 with 256.  Items of more than one
+      // round of points come first in their run, so that no dense one is left
+      // for the end (twelve slices of 512^2 to 2048^2 in one launch: 123 -> 107
+      // us, heaviest-first 109).
+      std::vector<WorkItem> logical;
+      std::vector<int> cost;
+      for (int s : bt.slices) {
+        const Geom& g = plan.geoms[size_t(plan.slice_geom[size_t(s)])];
+        for (int u = 0; u < int(g.iitems.size()); ++u) {
+          logical.push_back({s, u});
+          cost.push_back(256 + g.iitems[size_t(u)].end - g.iitems[size_t(u)].begin);
+        }
+      }
+      StageLaunch sl{Stage::FwdInterp, 0, plan.work.size() * sizeof(WorkItem), 0};
+      append_units_by_cost(plan.work, logical, cost, [&](const WorkItem& w) {
+        const SpreadItem& it = plan.geoms[size_t(plan.slice_geom[size_t(w.slice)])].iitems[size_t(w.unit)];
+        return it.end - it.begin > 256;
+      });
+      sl.n_work = int(plan.work.size() - sl.work_off / sizeof(WorkItem));
+      bt.fwd.push_back(sl);
       for (int L : Nts) add(bt.fwd, Stage::FwdRadial, L, false, true, angle_pairs);
     } else {
       for (int L : Nts) add(bt.fwd, Stage::FwdInterp, L, false, true, angle_pairs);
     }
     for (int L : Nts) add(bt.adj, Stage::AdjRadial, L, false, false, angle_pairs);
-    add(bt.adj, Stage::SpreadZero, 0, true, false, [](int s, const Geom& g, std::vector<WorkItem>& v) {
-      for (int u = 0; u < int(g.zero_tiles.size()); ++u) v.push_back({s, u});
-    });
     // spreading items of the whole batch, heaviest first (every tile has at
     // least one item, so the launch always exists)
     for (const StageLaunch& sl : heaviest_first(Stage::Spread, [](const Geom& g) -> const std::vector<SpreadItem>& {
            return g.items;
          }))
       bt.adj.push_back(sl);
+    add(bt.adj, Stage::SpreadShared, 0, true, false, [](int s, const Geom& g, std::vector<WorkItem>& v) {
+      for (int u = 0; u < kSharedTileUnits * int(g.shared.size()); ++u) v.push_back({s, u});
+    });
     for (int G : Gs) add(bt.adj, Stage::AdjCols, G, true, true, columns);
     for (int G : Gs) add(bt.adj, Stage::AdjRows, G, true, true, row_pairs);
     plan.batches.push_back(std::move(bt));
@@ -649,7 +712,7 @@ nr_status layout_plan(Plan& plan, std::string& err) {
         return NR_UNSUPPORTED_SIZE;
       }
     const Stage chain[] = {Stage::FwdRows, Stage::FwdCols, Stage::FwdInterp, Stage::FwdRadial, Stage::AdjRadial,
-                           Stage::SpreadZero, Stage::Spread, Stage::AdjCols, Stage::AdjRows};
+                           Stage::Spread, Stage::SpreadShared, Stage::AdjCols, Stage::AdjRows};
     for (Batch& bt : plan.batches) {
       const int n = int(bt.slices.size());
       const int first = bt.slices.front();
@@ -727,8 +790,8 @@ nr_status layout_plan(Plan& plan, std::string& err) {
     off = align_up(off + std::max<size_t>(1, g.pts.size()) * sizeof(int32_t), 256);
     g.off_items = off;
     off = align_up(off + g.items.size() * sizeof(SpreadItem), 256);
-    g.off_zero = off;
-    off = align_up(off + std::max<size_t>(1, g.zero_tiles.size()) * sizeof(int32_t), 256);
+    g.off_shared = off;
+    off = align_up(off + std::max<size_t>(1, g.shared.size()) * sizeof(SharedTile), 256);
     g.off_ipts = off;
     off = align_up(off + std::max<size_t>(1, g.ipts.size()) * sizeof(int32_t), 256);
     g.off_iitems = off;
@@ -772,7 +835,6 @@ std::vector<SliceDesc> slice_descs(const Plan& plan, char* d_ws) {
       d.cols = g.cols;
       d.tiles_x = g.tiles_x;
       d.n_items = int(g.items.size());
-      d.n_zero = int(g.zero_tiles.size());
       d.slot = int(k);
       d.vol_off = sl.vol_off;
       d.sino_off = sl.sino_off;
@@ -785,14 +847,14 @@ std::vector<SliceDesc> slice_descs(const Plan& plan, char* d_ws) {
       d.gxy = reinterpret_cast<const double*>(d_ws + g.off_gxy);
       d.flip = reinterpret_cast<const int32_t*>(d_ws + g.off_flip);
       char* slot = d_ws + plan.off_slot + size_t(bt.lane) * plan.slot_area + bt.slot_off[k];
-      const size_t ext_off = align_up(size_t((g.G / 2 + 4) / 4 * 4) * g.key.n * sizeof(f2), 256);
-      const size_t yh_off = align_up(ext_off + size_t(g.rows) * g.cols * sizeof(f2), 256);
+      const SliceScratch sc = slice_scratch(g);
       d.T = reinterpret_cast<float*>(slot);
-      d.ext = reinterpret_cast<float*>(slot + ext_off);
-      d.yh = reinterpret_cast<float*>(slot + yh_off);
+      d.ext = reinterpret_cast<float*>(slot + sc.ext);
+      d.yh = reinterpret_cast<float*>(slot + sc.yh);
+      d.parts = reinterpret_cast<float*>(slot + sc.parts);
       d.pts = reinterpret_cast<const int32_t*>(d_ws + g.off_pts);
       d.items = reinterpret_cast<const SpreadItem*>(d_ws + g.off_items);
-      d.zero_tiles = reinterpret_cast<const int32_t*>(d_ws + g.off_zero);
+      d.shared = reinterpret_cast<const SharedTile*>(d_ws + g.off_shared);
       d.itiles_x = g.itiles_x;
       d.rdisc = disc_radius(plan, g);
       d.jbits = g.jbits;

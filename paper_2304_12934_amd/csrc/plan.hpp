@@ -71,7 +71,8 @@ struct Geom {
   std::vector<int32_t> pts;         // point codes (a << jbits) | j, grouped by tile
   std::vector<int32_t> tile_start;  // tiles_x*tiles_y + 1 offsets into pts
   std::vector<SpreadItem> items;
-  std::vector<int32_t> zero_tiles;  // tiles written by atomic items: cleared first
+  std::vector<SharedTile> shared;   // tiles cut into several items
+  int n_parts = 0;                  // items of such tiles
   // interpolation bins (every point j >= 0 once, by the tile of its first tap)
   int itiles_x = 0, itiles_y = 0;
   std::vector<int32_t> ipts;
@@ -80,7 +81,7 @@ struct Geom {
   // batching reuse them)
   int bins_tile_w = -1, bins_tile_h = -1, bins_chunk = -1, ibins_chunk = -1;
   // workspace offsets (bytes)
-  size_t off_gxy = 0, off_flip = 0, off_pts = 0, off_items = 0, off_zero = 0, off_ipts = 0, off_iitems = 0;
+  size_t off_gxy = 0, off_flip = 0, off_pts = 0, off_items = 0, off_shared = 0, off_ipts = 0, off_iitems = 0;
 };
 
 // Tunable execution parameters: none changes results beyond float32 rounding
@@ -97,9 +98,9 @@ struct Tuning {
 };
 
 // Stages of the forward chain (FwdRows, FwdCols, FwdInterp, FwdRadial) and of the
-// adjoint chain (AdjRadial, SpreadZero, Spread, AdjCols, AdjRows).
+// adjoint chain (AdjRadial, Spread, SpreadShared, AdjCols, AdjRows).
 enum class Stage : int {
-  FwdRows = 0, FwdCols, FwdInterp, AdjRadial, Spread, AdjCols, AdjRows, SpreadZero, FwdRadial, Count
+  FwdRows = 0, FwdCols, FwdInterp, AdjRadial, Spread, AdjCols, AdjRows, SpreadShared, FwdRadial, Count
 };
 
 // One kernel launch of a batch: every unit of `stage` over the batch's
@@ -119,7 +120,7 @@ constexpr size_t kLastLevelCacheBytes = size_t(256) << 20;
 
 struct Batch {
   int lane = 0;                   // stream (and scratch area) the batch runs on
-  size_t bytes = 0;               // scratch bytes of its slices (T, ext, yh)
+  size_t bytes = 0;               // scratch bytes of its slices (T, ext, yh, parts)
   std::vector<int> slices;
   std::vector<size_t> slot_off;   // scratch offset of each slice inside its lane's slot area
   std::vector<StageLaunch> fwd, adj;
@@ -184,6 +185,10 @@ std::vector<SliceDesc> slice_descs(const Plan& plan, char* d_ws);
 // Radius (grid cells, from the origin of the spectrum) beyond which no
 // spreading tap lands and no interpolation tap reads.
 int disc_radius(const Plan& plan, const Geom& g);
+
+// Most points per item of a plan: the tuning's, or fewer where the plan's points
+// would make fewer than `items` items.
+int item_points(const Plan& plan, int64_t items);
 
 // Fills the spreading bins of one geometry (called by layout_plan).
 void build_spread_bins(const Plan& plan, Geom& g);

@@ -124,7 +124,8 @@ struct DSlice {
   NR_G float2* yh;
   const NR_G int32_t* pts;
   const NR_C SpreadItem* items;
-  const NR_G int32_t* zero_tiles;
+  const NR_C SharedTile* shared;
+  NR_G float2* parts;
   const NR_G int32_t* ipts;
   const NR_C SpreadItem* iitems;
   int itiles_x, rdisc, jbits;
@@ -148,7 +149,8 @@ __device__ __forceinline__ DSlice load_desc(const SliceDesc* descs, int slice) {
   d.yh = (NR_G float2*)s.yh;
   d.pts = (const NR_G int32_t*)s.pts;
   d.items = (const NR_C SpreadItem*)s.items;
-  d.zero_tiles = (const NR_G int32_t*)s.zero_tiles;
+  d.shared = (const NR_C SharedTile*)s.shared;
+  d.parts = (NR_G float2*)s.parts;
   d.ipts = (const NR_G int32_t*)s.ipts;
   d.iitems = (const NR_C SpreadItem*)s.iitems;
   d.itiles_x = s.itiles_x;
@@ -159,7 +161,7 @@ __device__ __forceinline__ DSlice load_desc(const SliceDesc* descs, int slice) {
 
 __device__ __forceinline__ SpreadItem load_item(const NR_C SpreadItem* items, int unit) {
   const NR_C SpreadItem& s = items[__builtin_amdgcn_readfirstlane(unit)];
-  return SpreadItem{s.tile, s.begin, s.end, s.flags, s.bound};
+  return SpreadItem{s.tile, s.begin, s.end, s.flags, s.bound, s.part};
 }
 
 // entry p of a launch's work list ({-1, 0} past its end)
@@ -253,7 +255,7 @@ struct InterpLds {
   // staged from one cell before the region (an even grid column), in pairs
   // of cells: RWP columns, an even count
   static constexpr int RWP = (RW + 2) / 2 * 2;
-  static constexpr int RS = RWP | 1;   // odd row stride (in complex cells)
+  static constexpr int RS = RWP;   // row stride in cells, even: rows start on 16 bytes
 };
 template <int W, int TW, int TH>
 struct SpreadLds {
@@ -312,6 +314,14 @@ __device__ __forceinline__ V buf_load(Rsrc r, uint32_t lane_off, uint32_t off) {
 #endif
   return v;
 }
+// 16 bytes per lane from memory to LDS at lds + 16 lane (lds uniform over the
+// wavefront); done once vmcnt has counted it (wait_lds_copies)
+__device__ __forceinline__ void buf_to_lds16(Rsrc r, uint32_t lane_off, float2* lds) {
+#ifdef __HIP_DEVICE_COMPILE__
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, int(lane_off), 0, 0, 0);
+#endif
+}
+__device__ __forceinline__ void wait_lds_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 typedef unsigned nr_u2 __attribute__((ext_vector_type(2)));
 typedef unsigned nr_u4 __attribute__((ext_vector_type(4)));
 template <class V>
@@ -565,6 +575,24 @@ __global__ __launch_bounds__(fft_threads(L)) void k_fwd_interp(LaunchArgs a, KBA
   NR_FOR_EACH_UNIT(a, wi) fwd_interp_unit<L, W, fft_threads(L)>(a, kb, wi, sbuf, int(threadIdx.x));
 }
 
+// The grid steps and the conjugation flag of each point's angle.
+template <int PER>
+__device__ __forceinline__ void load_angles(const DSlice& d, const int (&codes)[PER], double (&gx)[PER], double (&gy)[PER],
+                                            int (&fl)[PER]) {
+  struct Step {
+    double x, y;
+  };
+  const Rsrc steps = buf(d.gxy, 16u * uint32_t(d.na)), flips = buf(d.flip, 4u * uint32_t(d.na));
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const uint32_t ang = uint32_t(codes[k]) >> d.jbits;
+    const Step g = buf_load<Step>(steps, 16u * ang, 0u);
+    gx[k] = g.x;
+    gy[k] = g.y;
+    fl[k] = buf_load<int>(flips, 4u * ang, 0u);
+  }
+}
+
 // The item's descriptor, entry, point codes and angle tables (slots past the
 // item's end repeat its first point; items are never empty).
 template <int T, int PER, class LA>
@@ -573,58 +601,38 @@ __device__ __forceinline__ void interp_fetch_points(const LA& a, const WorkItem 
                                                     int (&fl)[PER], const int tid) {
   d = load_desc(a.descs, wi.slice);
   it = load_item(d.iitems, wi.unit);
+  const uint32_t count = uint32_t(it.end - it.begin);
+  const Rsrc pts = buf(d.ipts + it.begin, 4u * count);
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    const int e = tid + k * T;
-    codes[k] = d.ipts[it.begin + (e < it.end - it.begin ? e : 0)];
+    const uint32_t e = uint32_t(tid + k * T);
+    codes[k] = buf_load<int>(pts, 4u * (e < count ? e : 0u), 0u);
   }
-#pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int ang = codes[k] >> d.jbits;
-    gx[k] = d.gxy[2 * ang];
-    gy[k] = d.gxy[2 * ang + 1];
-    fl[k] = d.flip[ang];
-  }
+  load_angles<PER>(d, codes, gx, gy, fl);
 }
 
-// The tile region of an item: its first row and (even) first column, one
-// cell before the tile's margin, so that every 16-byte load takes two cells
-// of a row (grid rows are 64-byte aligned and hold an even number of cells).
-// Thread tid loads pairs tid, tid + T, ... of the region into registers;
-// staged cells off the grid are never read by a point, so the address is
-// clamped and the load kept unconditional.
+// Stages an item's tile region in LDS: from its first row and (even) first
+// column, one cell before the tile's margin, so that every 16 bytes hold two
+// cells of a row (grid rows are 64-byte aligned and hold an even number of
+// cells).  A wavefront copies a row at a time, straight from memory to LDS:
+// no registers hold the cells and no vector instruction but one addition per
+// row moves them (staging through registers, with a division per cell pair and
+// the grid's edges clamped, was a quarter of the kernel's vector
+// instructions).  Cells off the grid are never read by a point: they come out
+// as zeros or as cells of the neighbouring row.
 template <int W, int T>
-struct InterpStage {
-  static constexpr int PAIRS = InterpLds<W>::RWP / 2;
-  static constexpr int N = (InterpLds<W>::RH * PAIRS + T - 1) / T;
-};
-template <int W, int T>
-__device__ __forceinline__ void interp_stage_load(const DSlice& d, const SpreadItem& it, float4 (&v)[InterpStage<W, T>::N],
-                                                  const int tid) {
-  constexpr int TW = kInterpTileW, TH = kInterpTileH, PAIRS = InterpStage<W, T>::PAIRS;
-  constexpr int COUNT = InterpLds<W>::RH * PAIRS;
+__device__ __forceinline__ void interp_stage(const DSlice& d, const SpreadItem& it, float2* reg, const int tid) {
+  constexpr int TW = kInterpTileW, TH = kInterpTileH, RH = InterpLds<W>::RH, RS = InterpLds<W>::RS;
+  constexpr int PAIRS = InterpLds<W>::RWP / 2;
+  static_assert(PAIRS <= 64 && RS % 2 == 0, "one row per wavefront copy, on 16 bytes");
   const int r0 = (it.tile / d.itiles_x) * TH - 1, c0 = (it.tile % d.itiles_x) * TW - 2;
-  const NR_G float4* __restrict__ ext4 = reinterpret_cast<const NR_G float4*>(d.ext);
+  const Rsrc grid = buf(d.ext, uint32_t(d.rows) * uint32_t(d.cols) * 8u);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  if (lane < PAIRS) {
 #pragma unroll
-  for (int z = 0; z < InterpStage<W, T>::N; ++z) {
-    const int c = min(tid + z * T, COUNT - 1);
-    const int rl = c / PAIRS, pl = c % PAIRS;
-    const int r = min(max(r0 + rl, 0), d.rows - 1);
-    const int cc = min(max(c0 + 2 * pl, 0), d.cols - 2);
-    v[z] = ext4[(size_t(r) * d.cols + cc) >> 1];
-  }
-}
-template <int W, int T>
-__device__ __forceinline__ void interp_stage_store(float2* reg, const float4 (&v)[InterpStage<W, T>::N], const int tid) {
-  constexpr int PAIRS = InterpStage<W, T>::PAIRS, RS = InterpLds<W>::RS;
-  constexpr int COUNT = InterpLds<W>::RH * PAIRS;
-#pragma unroll
-  for (int z = 0; z < InterpStage<W, T>::N; ++z) {
-    const int c = tid + z * T;
-    if (COUNT % T == 0 || c < COUNT) {
-      const int rl = c / PAIRS, pl = c % PAIRS;
-      reg[rl * RS + 2 * pl] = make_float2(v[z].x, v[z].y);
-      reg[rl * RS + 2 * pl + 1] = make_float2(v[z].z, v[z].w);
+    for (int z = 0; z < (RH + T / 64 - 1) / (T / 64); ++z) {
+      const int rl = wave + z * (T / 64);
+      if (RH % (T / 64) == 0 || rl < RH) buf_to_lds16(grid, uint32_t(((r0 + rl) * d.cols + c0) * 8 + lane * 16), reg + rl * RS);
     }
   }
 }
@@ -666,7 +674,7 @@ __device__ __forceinline__ void interp_compute(const LA& a, const KB& kb, const 
       acc.y = fmaf(wx[i], r.y, acc.y);
     }
     if (fl[k]) acc.y = -acc.y;
-    d.yh[__umul24(uint32_t(code >> d.jbits), uint32_t(d.H)) + j] = c_scale(acc, inv);
+    d.yh[__umul24(uint32_t(code) >> d.jbits, uint32_t(d.H)) + uint32_t(j)] = c_scale(acc, inv);
   }
 }
 
@@ -674,10 +682,10 @@ __device__ __forceinline__ void interp_compute(const LA& a, const KB& kb, const 
 // points whose first tap lies in it.  The workgroup stages the tile with the
 // W-1 cells the footprints reach past it and a one-cell margin on each side,
 // then every thread interpolates its points from LDS.
-// The staged cells are complex values with an odd row stride (neighbouring
-// lanes take neighbouring points of one line, about two cells apart): a
-// point's taps along a row are read two cells per LDS instruction, which
-// measured 2 % faster than separate real and imaginary planes.
+// The staged cells are complex values (neighbouring lanes take neighbouring
+// points of one line, about two cells apart): a point's taps along a row are
+// read two cells per LDS instruction, which measured 2 % faster than separate
+// real and imaginary planes.
 template <int W, class LA, class KB>
 __device__ __forceinline__ void interp_tiles_unit(const LA& a, const KB& kb, const WorkItem wi, float2* reg, const int tid) {
   constexpr int T = 256, PER = kMaxChunk / T;
@@ -685,48 +693,46 @@ __device__ __forceinline__ void interp_tiles_unit(const LA& a, const KB& kb, con
   SpreadItem it;
   int codes[PER], fl[PER];
   double gx[PER], gy[PER];
-  float4 stg[InterpStage<W, T>::N];
   interp_fetch_points<T>(a, wi, d, it, codes, gx, gy, fl, tid);
-  interp_stage_load<W, T>(d, it, stg, tid);
-  interp_stage_store<W, T>(reg, stg, tid);
+  interp_stage<W, T>(d, it, reg, tid);
+  wait_lds_copies();
   __syncthreads();
   interp_compute<W, T>(a, kb, d, it, codes, gx, gy, fl, reg, tid);
 }
 
-// Two work items per workgroup, b and n-1-b of the heaviest-first list: both
-// items' point loads (descriptor, entry, codes, angle tables: a chain of
-// dependent round trips) are issued at once, so the second item's chain is
-// hidden behind the first item's staging and interpolation; the second tile
-// is staged after the first is interpolated.  Measured on 2560^2 slices,
-// 1024 angles: 35.9 -> 32.5 us per slice (b with b + gridDim.x), 32.25 with
-// the heavy-light pairing; staging the second tile into registers up front
-// as well took 102 VGPRs (four workgroups per CU instead of six) and ran
-// 36.2 us.
+// With pair_units two work items per workgroup, neighbours in the XCD's run of
+// the list: both items' point loads (descriptor, entry, codes, angle tables: a
+// chain of dependent round trips) are issued at once, so the second item's
+// chain is hidden behind the first item's staging and interpolation; the
+// second tile is staged after the first is interpolated.  Measured on 2560^2
+// slices, 1024 angles, eight per launch: 35.9 -> 32.5 us per slice.
+// The stage is bound by its reads of the grid: with neighbouring tiles on one
+// XCD and the tiles staged without registers it runs 32.0 us.
 template <int W>
 __global__ __launch_bounds__(256) void k_interp_tiles(LaunchArgs a, KBArgs kb) {
   constexpr int T = 256, PER = kMaxChunk / T;
-  __shared__ float2 reg[InterpLds<W>::RH * InterpLds<W>::RS];
+  __shared__ __attribute__((aligned(16))) float2 reg[InterpLds<W>::RH * InterpLds<W>::RS];
   const int tid = int(threadIdx.x);
-  const int b0 = int(blockIdx.x), b1 = a.n_work - 1 - b0;
-  const WorkItem w0 = work_entry(a, b0);
-  const WorkItem w1 = b1 > b0 ? work_entry(a, b1) : WorkItem{-1, 0};
+  // paired: the k-th entry of the XCD's run with the k-th from its end
+  const int b = int(blockIdx.x), b1 = a.n_work - 8 - (b & ~7) + (b & 7);
+  const WorkItem w0 = work_entry(a, b);
+  const WorkItem w1 = a.pair_units && b1 > b ? work_entry(a, b1) : WorkItem{-1, 0};
   DSlice d0, d1;
   SpreadItem i0, i1;
   int c0[PER], f0[PER], c1[PER], f1[PER];
   double x0[PER], y0[PER], x1[PER], y1[PER];
-  float4 s0[InterpStage<W, T>::N], s1[InterpStage<W, T>::N];
   if (w0.slice >= 0) interp_fetch_points<T>(a, w0, d0, i0, c0, x0, y0, f0, tid);
   if (w1.slice >= 0) interp_fetch_points<T>(a, w1, d1, i1, c1, x1, y1, f1, tid);
-  if (w0.slice >= 0) interp_stage_load<W, T>(d0, i0, s0, tid);
   if (w0.slice >= 0) {
-    interp_stage_store<W, T>(reg, s0, tid);
+    interp_stage<W, T>(d0, i0, reg, tid);
+    wait_lds_copies();
     __syncthreads();
     interp_compute<W, T>(a, kb, d0, i0, c0, x0, y0, f0, reg, tid);
   }
   if (w1.slice >= 0) {
-    interp_stage_load<W, T>(d1, i1, s1, tid);
     __syncthreads();   // the first tile's reads are done
-    interp_stage_store<W, T>(reg, s1, tid);
+    interp_stage<W, T>(d1, i1, reg, tid);
+    wait_lds_copies();
     __syncthreads();
     interp_compute<W, T>(a, kb, d1, i1, c1, x1, y1, f1, reg, tid);
   }
@@ -841,23 +847,45 @@ __global__ void k_fill_zero(float4* p, size_t n4) {
     p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-// clear the tiles that several work items accumulate into
+// Adds up the parts of a tile that several items share, in their order: unit u
+// is one fourth of the rows of shared tile u / 4.  Bound by reading the parts
+// (2560^2, 1024 angles: 422 parts of 162 tiles, 9 MB read and written, 2.3 us
+// per slice; sixteen-fold smaller units ran 4.2); the loads of eight parts are
+// in flight at once for the tile at the origin, whose parts number in the
+// tens.  The parts replace global float atomics into a cleared tile, which
+// meet in the memory behind the XCDs' caches: the sums no longer depend on the
+// order of arrival, and cutting a tile costs a write and a read of its cells
+// per part (four 1024^2 slices of 901 angles: whole adjoint 139 -> 124 us; seven
+// 320^2 slices of 451: 79 -> 58).
 template <int TW, int TH, class LA>
-__device__ __forceinline__ void spread_zero_unit(const LA& a, const WorkItem wi, const int tid) {
-
+__device__ __forceinline__ void spread_shared_unit(const LA& a, const WorkItem wi, const int tid) {
   const DSlice d = load_desc(a.descs, wi.slice);
-  const int t = d.zero_tiles[wi.unit];
-  const int r0 = (t / d.tiles_x) * TH, c0 = (t % d.tiles_x) * TW;
-  NR_G float2* ext = d.ext;
-  for (int c = tid; c < TW * TH; c += 256) {
-    const int r = r0 + c / TW, cc = c0 + c % TW;
-    if (r < d.rows && cc < d.cols) ext[size_t(r) * d.cols + cc] = make_float2(0.f, 0.f);
+  const int u = __builtin_amdgcn_readfirstlane(wi.unit);
+  const NR_C SharedTile& sh = d.shared[u / kSharedTileUnits];
+  const int t = sh.tile, first = sh.first, count = sh.count;
+  constexpr int CELLS = TW * TH / kSharedTileUnits, PER = CELLS / 256;
+  static_assert(TH % kSharedTileUnits == 0 && CELLS % 256 == 0, "whole rows, whole rounds");
+  const int c0 = (u % kSharedTileUnits) * CELLS;
+  const NR_G float2* __restrict__ p = d.parts + size_t(first) * (TW * TH) + c0 + tid;
+  float2 sum[PER];
+#pragma unroll
+  for (int z = 0; z < PER; ++z) sum[z] = make_float2(0.f, 0.f);
+#pragma unroll 8
+  for (int k = 0; k < count; ++k)
+#pragma unroll
+    for (int z = 0; z < PER; ++z) sum[z] = c_add(sum[z], p[k * (TW * TH) + z * 256]);
+  const int r0 = (t / d.tiles_x) * TH, cc0 = (t % d.tiles_x) * TW;
+#pragma unroll
+  for (int z = 0; z < PER; ++z) {
+    const int c = c0 + tid + z * 256;
+    const int r = r0 + c / TW, cc = cc0 + c % TW;
+    if (r < d.rows && cc < d.cols) d.ext[size_t(r) * d.cols + cc] = sum[z];
   }
 }
 
 template <int TW, int TH>
-__global__ __launch_bounds__(256) void k_spread_zero(LaunchArgs a) {
-  NR_FOR_EACH_UNIT(a, wi) spread_zero_unit<TW, TH>(a, wi, int(threadIdx.x));
+__global__ __launch_bounds__(256) void k_spread_shared(LaunchArgs a) {
+  NR_FOR_EACH_UNIT(a, wi) spread_shared_unit<TW, TH>(a, wi, int(threadIdx.x));
 }
 
 // One work item = one grid tile (TH rows x TW columns) and a range of the
@@ -873,8 +901,8 @@ __global__ __launch_bounds__(256) void k_spread_zero(LaunchArgs a) {
 // The LDS tile carries a W-cell apron on every side, which holds the whole
 // footprint of every listed point, so each point adds its W x W taps with no
 // bounds test (no divergence); the apron is dropped at the end.  Single-item
-// tiles are then stored plainly (every cell, zeros included); shared tiles
-// are added with global float atomics.
+// tiles are then stored plainly (every cell, zeros included); the items of a
+// shared tile store theirs to their parts (spread_shared_unit).
 // A spreading item's points are held in registers between the loads and the
 // accumulation, as five arrays (gathered in one aggregate they were placed in
 // scratch memory): slot k of thread tid is entry tid + k*T of the item.
@@ -896,11 +924,12 @@ __device__ __forceinline__ void spread_fetch_codes(const LA& a, const WorkItem w
                                                    int (&code)[PER], const int tid) {
   d = load_desc(a.descs, wi.slice);
   it = load_item(d.items, wi.unit);
-  const int count = it.end - it.begin;   // at most kMaxChunk
+  const uint32_t count = uint32_t(it.end - it.begin);   // at most kMaxChunk
+  const Rsrc pts = buf(d.pts + it.begin, 4u * count);   // count = 0: every load is zero
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    const int e = tid + k * T;
-    code[k] = count > 0 ? d.pts[it.begin + (e < count ? e : 0)] : 0;
+    const uint32_t e = uint32_t(tid + k * T);
+    code[k] = buf_load<int>(pts, 4u * (e < count ? e : 0u), 0u);
   }
 }
 
@@ -910,12 +939,10 @@ __device__ __forceinline__ void spread_fetch_values(const DSlice& d, const int (
                                                     double (&gx)[PER], double (&gy)[PER], int (&fl)[PER]) {
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    const int ang = code[k] >> d.jbits;
-    v[k] = d.yh[__umul24(uint32_t(ang), uint32_t(d.H)) + (code[k] & ((1 << d.jbits) - 1))];
-    gx[k] = d.gxy[2 * ang];
-    gy[k] = d.gxy[2 * ang + 1];
-    fl[k] = d.flip[ang];
+    const uint32_t ang = uint32_t(code[k]) >> d.jbits;
+    v[k] = d.yh[__umul24(ang, uint32_t(d.H)) + (uint32_t(code[k]) & ((1u << d.jbits) - 1u))];
   }
+  load_angles<PER>(d, code, gx, gy, fl);
 }
 
 template <int W, int TW, int TH, int T, int PER, class LA, class KB>
@@ -1011,7 +1038,6 @@ __device__ __forceinline__ void spread_accumulate(const LA& a, const KB& kb, con
     }
   }
   __syncthreads();
-  const bool shared_tile = it.flags & kItemAtomic;
   const float inv_q = nonfinite ? __int_as_float(0x7fc00000) : (q > 0.f ? __builtin_amdgcn_rcpf(q) : 0.f);
   // the origin's W x W footprint in apron coordinates (DC items only)
   int dcx = 0, dcy = 0;
@@ -1028,13 +1054,18 @@ __device__ __forceinline__ void spread_accumulate(const LA& a, const KB& kb, con
   constexpr int STEP = T / TW;
   const int cl = tid % TW, rl0 = tid / TW;
   const int cc = c0 + cl;
-  NR_G float2* dst = d.ext + size_t(r0 + rl0) * d.cols + cc;
-  const size_t dstep = size_t(STEP) * d.cols;
-  const bool col_ok = cc < d.cols;
+  const bool part = it.flags & kItemPart;
+  const int pitch = part ? TW : d.cols;
+  NR_G float2* dst = part ? d.parts + size_t(it.part) * (TW * TH) + rl0 * TW + cl
+                          : d.ext + size_t(r0 + rl0) * d.cols + cc;
+  const size_t dstep = size_t(STEP) * pitch;
+  const int rows = part ? TH : d.rows - r0;   // rows and columns to write
+  const bool col_ok = part || cc < d.cols;
+  const bool nt = a.stream_stores && !part;
 #pragma unroll
   for (int s = 0; s < TH / STEP; ++s) {
     const int rl = rl0 + s * STEP;
-    if (col_ok && r0 + rl < d.rows) {
+    if (col_ok && rl < rows) {
       const int ai = (rl + W) * TS + cl + W;
       float re = float(acc_re[ai]) * inv_q;
       const float im = float(acc_im[ai]) * inv_q;
@@ -1050,15 +1081,10 @@ __device__ __forceinline__ void spread_accumulate(const LA& a, const KB& kb, con
           re += dc * wi * wl;
         }
       }
-      if (shared_tile) {
-        atomicAdd((NR_G float*)&dst->x, re);
-        atomicAdd((NR_G float*)&dst->y, im);
-      } else {
-        if (a.stream_stores)
-          store_nt(dst, make_float2(re, im));
-        else
-          *dst = make_float2(re, im);
-      }
+      if (nt)
+        store_nt(dst, make_float2(re, im));
+      else
+        *dst = make_float2(re, im);
     }
     dst += dstep;
   }
@@ -1077,8 +1103,8 @@ __device__ __forceinline__ void spread_tiles_unit(const LA& a, const KB& kb, con
   spread_accumulate<W, TW, TH, T>(a, kb, d, it, NR_SPREAD_PTS(p), acc, red, nonfinite, tid);
 }
 
-// Two work items per workgroup: b and n-1-b of the list, which is sorted
-// heaviest first, so that every workgroup pairs a heavy item (bound by its
+// With pair_units two work items per workgroup: b and n-1-b of the list, which is
+// sorted heaviest first, so that every workgroup pairs a heavy item (bound by its
 // taps) with a light one (bound by its tile stores) and the launch keeps a
 // like mix of both from start to end.  An item's loads form a chain of four
 // dependent round trips (work entry, descriptor and item, point codes,
@@ -1097,7 +1123,7 @@ __global__ __launch_bounds__(kSpreadThreads) void k_spread_tiles(LaunchArgs a, K
   const int tid = int(threadIdx.x);
   const int b0 = int(blockIdx.x), b1 = a.n_work - 1 - b0;
   const WorkItem w0 = work_entry(a, b0);
-  const WorkItem w1 = b1 > b0 ? work_entry(a, b1) : WorkItem{-1, 0};
+  const WorkItem w1 = a.pair_units && b1 > b0 ? work_entry(a, b1) : WorkItem{-1, 0};
   constexpr int PER = kMaxChunk / T;
   DSlice d0, d1;
   SpreadItem i0, i1;
@@ -1348,8 +1374,8 @@ __device__ __forceinline__ void persist_unit(const LA& a, const KB& kb, int stag
 #undef NR_CASE
       }
       return;
-    case StageKind::SpreadZero:
-      spread_zero_unit<64, 32>(a, wi, tid);
+    case StageKind::SpreadShared:
+      spread_shared_unit<64, 32>(a, wi, tid);
       return;
     case StageKind::Spread: {
       spread_tiles_unit<W, 64, 32, kPersistThreads>(a, kb, wi, reinterpret_cast<int*>(lds), red, nonfinite, tid);
@@ -1475,12 +1501,22 @@ hipError_t launch(K kernel, int threads, int n, hipStream_t st, Args... args) {
 #define NR_LENGTHS(X) \
   X(16) X(32) X(64) X(128) X(256) X(512) X(1024) X(2048) X(4096) X(8192) X(80) X(160) X(320) X(640) X(1280) X(2560) X(5120)
 
+// interpolation and spreading launches with at least this many items run two
+// per workgroup (k_interp_tiles, k_spread_tiles); below, about six rounds of
+// resident workgroups, the parallelism is worth more: us per slice, paired and
+// not, of one 2560^2 slice (5440 items) spreading 60.8 and 54.4, interpolation
+// 58.3 and 50.8; of 2048^2 (361 angles) spreading 33.7 and 29.1; of 1280^2
+// (256 angles) 16.4 and 13.3; of 64^2 (45 angles) 4.3 and 3.2
+constexpr int kPairItemsMin = 8192;
+
 template <int W>
-hipError_t launch_spread(const LaunchArgs& a, const KBArgs& kb, int tw, int th, hipStream_t st, bool zero) {
+hipError_t launch_spread(const LaunchArgs& args, const KBArgs& kb, int tw, int th, hipStream_t st, bool shared) {
+  LaunchArgs a = args;
+  a.pair_units = a.n_work >= kPairItemsMin ? 1 : 0;
 #define NR_TILE(w, h)                                                               \
   if (tw == w && th == h)                                                           \
-    return zero ? launch(k_spread_zero<w, h>, 256, a.n_work, st, a)                 \
-                : launch(k_spread_tiles<W, w, h>, kSpreadThreads, (a.n_work + 1) / 2, st, a, kb);
+    return shared ? launch(k_spread_shared<w, h>, 256, a.n_work, st, a)             \
+                : launch(k_spread_tiles<W, w, h>, kSpreadThreads, a.pair_units ? (a.n_work + 1) / 2 : a.n_work, st, a, kb);
   NR_TILE(64, 32)
   NR_TILE(32, 32)
   NR_TILE(64, 64)
@@ -1517,9 +1553,12 @@ hipError_t launch_stage(StageKind stage, int L, const LaunchArgs& a, const KBArg
     }
     case StageKind::FwdInterp:
       if (L == 0) {   // tiled interpolation (the radial pass is its own stage)
-        if (W == 6) return launch(k_interp_tiles<6>, 256, (a.n_work + 1) / 2, st, a, kb);
-        if (W == 7) return launch(k_interp_tiles<7>, 256, (a.n_work + 1) / 2, st, a, kb);
-        return launch(k_interp_tiles<8>, 256, (a.n_work + 1) / 2, st, a, kb);
+        LaunchArgs b = a;
+        b.pair_units = a.n_work >= kPairItemsMin ? 1 : 0;
+        const int grid = b.pair_units ? (a.n_work + 15) / 16 * 8 : a.n_work;
+        if (W == 6) return launch(k_interp_tiles<6>, 256, grid, st, b, kb);
+        if (W == 7) return launch(k_interp_tiles<7>, 256, grid, st, b, kb);
+        return launch(k_interp_tiles<8>, 256, grid, st, b, kb);
       }
       switch (L) {
 #define NR_CASE(l)                                                                          \
@@ -1545,12 +1584,12 @@ hipError_t launch_stage(StageKind stage, int L, const LaunchArgs& a, const KBArg
 #undef NR_CASE
       }
       break;
-    case StageKind::SpreadZero:
+    case StageKind::SpreadShared:
     case StageKind::Spread: {
-      const bool zero = stage == StageKind::SpreadZero;
-      if (W == 6) return launch_spread<6>(a, kb, tile_w, tile_h, st, zero);
-      if (W == 7) return launch_spread<7>(a, kb, tile_w, tile_h, st, zero);
-      return launch_spread<8>(a, kb, tile_w, tile_h, st, zero);
+      const bool shared = stage == StageKind::SpreadShared;
+      if (W == 6) return launch_spread<6>(a, kb, tile_w, tile_h, st, shared);
+      if (W == 7) return launch_spread<7>(a, kb, tile_w, tile_h, st, shared);
+      return launch_spread<8>(a, kb, tile_w, tile_h, st, shared);
     }
     case StageKind::AdjCols:
       switch (L) {

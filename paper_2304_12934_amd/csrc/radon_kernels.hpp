@@ -22,7 +22,7 @@ struct LaunchArgs {
   int fbp_order;
   float fbp_inv_cutoff;
   int stream_stores;        // 1: the forward columns and the spreading store their rows non-temporally
-  int pair_units;           // set by launch_stage: 1 when the forward columns run two units per workgroup
+  int pair_units;           // set by launch_stage: 1 when workgroups run two units each (columns, tile items)
 };
 
 // Arguments of a persistent launch (one batch): the per-XCD queues of
@@ -46,7 +46,7 @@ struct KBArgs {
 };
 
 // The stage kernels (same order as nr::Stage).
-enum class StageKind : int { FwdRows = 0, FwdCols, FwdInterp, AdjRadial, Spread, AdjCols, AdjRows, SpreadZero, FwdRadial };
+enum class StageKind : int { FwdRows = 0, FwdCols, FwdInterp, AdjRadial, Spread, AdjCols, AdjRows, SpreadShared, FwdRadial };
 
 // One grid-stride launch of `stage` over its work list; L = FFT length of the
 // slices in the list (unused by the spreading stages).

@@ -16,10 +16,6 @@ struct PriorArgs {
 // accumulate is false and value is null); value (if not null) = H(f)
 hipError_t launch_qggmrf(const float* f, float* grad, double* value, int nz, int n, const PriorArgs& pr,
                          float scale, hipStream_t st, bool accumulate = true);
-// s -= b
-hipError_t launch_residual(float* s, const float* b, size_t count, hipStream_t st);
-// s -= b and value = 1/2 sum (s - b)^2
-hipError_t launch_residual_norm(float* s, const float* b, size_t count, double* value, hipStream_t st);
 // Slots of the float64 MBIR state array (kStCount doubles on the device).
 enum {
   kStT = 0,          // momentum parameter t_k

@@ -440,7 +440,8 @@ nr_status nr_plan_check(nr_plan* plan, nr_stream stream);
  * info[0] = oversampled grid G, info[1] = spreading tiles, info[2] = tile
  * point entries, info[3] = spreading work items, info[4] = polynomial degree,
  * info[5] = scratch slots (slices per batch), info[6] = batches,
- * info[7] = kernel launches of one forward + adjoint pass. */
+ * info[7] = kernel launches of a forward and an adjoint call (radon_normal,
+ * which joins their radial stages, takes one fewer per detector length). */
 nr_status nr_plan_info(const nr_plan* plan, int32_t index, int64_t* info, int32_t count);
 
 #ifdef __cplusplus

@@ -294,11 +294,15 @@ nr_status run_batches(nr_plan* plan, bool fwd, const float* b, bool adj, const f
   for (size_t bi = 0; !persist && bi < p.batches.size(); ++bi) {
     const nr::Batch& bt = p.batches[bi];
     hipStream_t bs = lane_stream(bt);
+    // a forward whose sinogram is the adjoint's input: the forward's radial
+    // stage runs the adjoint's too (while stages are timed, each on its own)
+    const bool join_radial = fwd && adj && !fbp && sino_in == sino_out && p.tune.interp_mode == 0 && !plan->profiling;
     std::vector<const nr::StageLaunch*> seq;
     if (fwd)
       for (const nr::StageLaunch& sl : bt.fwd) seq.push_back(&sl);
     if (adj)
-      for (const nr::StageLaunch& sl : bt.adj) seq.push_back(&sl);
+      for (const nr::StageLaunch& sl : bt.adj)
+        if (!(join_radial && sl.stage == nr::Stage::AdjRadial)) seq.push_back(&sl);
     // Lanes start skewed: lane l's first batch waits until lane l-1's first
     // batch has issued 1/nl of its stages, so concurrent lanes run different
     // kinds of stage (transforms, gathers, scatters) rather than the same one.
@@ -339,6 +343,7 @@ nr_status run_batches(nr_plan* plan, bool fwd, const float* b, bool adj, const f
         la.n_work = sl.n_work;
         la.stream_stores = bt.bytes > nr::kLastLevelCacheBytes ? 1 : 0;
         // the stage that writes the sinogram rows subtracts b as it stores them
+        la.radial_adjoint = join_radial && sl.stage == nr::Stage::FwdRadial ? 1 : 0;
         if (sl.stage == nr::Stage::FwdRadial || (sl.stage == nr::Stage::FwdInterp && sl.L > 0)) la.sino_sub = b;
         e = timed(plan, stage_event_id(sl.stage), bs, [&] {
           return nrk::launch_stage(static_cast<nrk::StageKind>(int(sl.stage)), sl.L, la, kb, p.kb.W,

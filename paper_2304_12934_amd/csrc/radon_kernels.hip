@@ -520,7 +520,9 @@ __device__ __forceinline__ float2 interp_point(const DSlice& d, int halo, int co
 // bin m (t = m - N_t/2) is output index t mod N_t.  With a.sino_sub the
 // data b are subtracted as the rows are stored (the residual R f - b of the
 // data term, Sec. 3 eq. "objfn"), so no separate pass re-reads them.
-template <int L, int T, class LA>
+// With KEEP the stored values replace those of s, packed the same way (the
+// input of A1).
+template <int L, int T, bool KEEP = false, class LA>
 __device__ __forceinline__ void store_sino_rows(const LA& a, const DSlice& d, int a0, bool has1, Lds s,
                                                 int tid) {
   const size_t off = d.sino_off + size_t(a0) * L;
@@ -529,16 +531,19 @@ __device__ __forceinline__ void store_sino_rows(const LA& a, const DSlice& d, in
     const float* __restrict__ b0 = a.sino_sub + off;
     const float* __restrict__ b1 = has1 ? b0 + L : b0;   // loads stay unconditional
     NR_STRIDED(m, L, T) {
-      const float2 z = s[wrap_index<L>(m + L / 2)];
+      float2& z = s[wrap_index<L>(m + L / 2)];
       const float c0 = b0[m], c1 = b1[m];
-      o0[m] = z.x - c0;
-      if (has1) o0[L + m] = z.y - c1;
+      const float v0 = z.x - c0, v1 = z.y - c1;
+      o0[m] = v0;
+      if (has1) o0[L + m] = v1;
+      if (KEEP) z = make_float2(v0, has1 ? v1 : 0.f);
     }
   } else {
     NR_STRIDED(m, L, T) {
-      const float2 z = s[wrap_index<L>(m + L / 2)];
+      float2& z = s[wrap_index<L>(m + L / 2)];
       o0[m] = z.x;
       if (has1) o0[L + m] = z.y;
+      if (KEEP && !has1) z.y = 0.f;
     }
   }
 }
@@ -738,10 +743,51 @@ __global__ __launch_bounds__(256) void k_interp_tiles(LaunchArgs a, KBArgs kb) {
   }
 }
 
+// Filtered back-projection weight of half-line index j of an L-point line:
+// (pi/n_angles) |k| B(k) with k = j/L cycles per pixel and B = 1 (ramp) or
+// 1/(1 + (k/cutoff)^(2 order)) (Butterworth).
+template <class LA>
+__device__ __forceinline__ float fbp_weight(const LA& a, int j, int L, int n_angles) {
+  const float k = float(j) / float(L);
+  float w = k;
+  if (a.fbp_filter == 1) {
+    const float x = k * a.fbp_inv_cutoff, x2 = x * x;
+    float pw = 1.f;
+    for (int i = 0; i < a.fbp_order; ++i) pw *= x2;
+    w = k / (1.f + pw);
+  }
+  return w * (3.14159265358979f / float(n_angles));
+}
+
+// The half-lines of angles a0 and a0 + 1 from the packed transform of their
+// sinogram rows in s, weights c_j/N_t.
+template <int L, int T, class LA>
+__device__ __forceinline__ void store_half_lines(const LA& a, const DSlice& d, int a0, bool has1, Lds s, const int tid) {
+  const int H = L / 2 + 1;
+  NR_G float2* __restrict__ o0 = d.yh + size_t(a0) * H;
+  const float inv = 1.0f / float(L);
+  NR_STRIDED(j, H, T) {
+    const float2 z1 = s[j], z2 = s[j == 0 ? 0 : L - j];
+    float w = (j == 0 || j == L / 2) ? inv : 2.0f * inv;
+    if (a.fbp_filter >= 0) w *= fbp_weight(a, j, L, d.na);
+    float2 A = make_float2(0.5f * w * (z1.x + z2.x), 0.5f * w * (z1.y - z2.y));
+    float2 B = make_float2(0.5f * w * (z1.y + z2.y), 0.5f * w * (z2.x - z1.x));
+    if (d.shift) {   // transpose of the forward's phase
+      const float2 q = c_conj(d.shift[j]);
+      A = c_mul(A, q);
+      B = c_mul(B, q);
+    }
+    o0[j] = A;
+    if (has1) o0[H + j] = B;
+  }
+}
+
 // F4 after k_interp_tiles: per pair of angles, the Hermitian completions of
 // the two half-lines packed as Z = X + iY, the inverse DFT along the line and
-// the real sinogram rows.
-template <int L, int T, class LA>
+// the real sinogram rows.  With ADJ (the residual's adjoint follows, as in
+// radon_normal), the rows go back through A1 at once: the same values that A1
+// would read from memory, one launch and one read of the sinogram fewer.
+template <int L, int T, bool ADJ, class LA>
 __device__ __forceinline__ void fwd_radial_unit(const LA& a, const WorkItem wi, float2* sbuf, const int tid) {
   const Lds s{sbuf};
   constexpr int H = L / 2 + 1;
@@ -767,35 +813,24 @@ __device__ __forceinline__ void fwd_radial_unit(const LA& a, const WorkItem wi, 
   }
   __syncthreads();
   fft_lds<L, T, true>(s, d.tw_Nt, tid);
-  store_sino_rows<L, T>(a, d, a0, has1, s, tid);
+  store_sino_rows<L, T, ADJ>(a, d, a0, has1, s, tid);
   __syncthreads();
+  if constexpr (ADJ) {
+    fft_lds<L, T, false>(s, d.tw_Nt, tid);
+    store_half_lines<L, T>(a, d, a0, has1, s, tid);
+    __syncthreads();
+  }
 }
 
-template <int L>
+template <int L, bool ADJ>
 __global__ __launch_bounds__(fft_threads(L)) void k_fwd_radial(LaunchArgs a) {
   __shared__ float2 sbuf[lds_elems<L>()];
-  NR_FOR_EACH_UNIT(a, wi) fwd_radial_unit<L, fft_threads(L)>(a, wi, sbuf, int(threadIdx.x));
+  NR_FOR_EACH_UNIT(a, wi) fwd_radial_unit<L, fft_threads(L), ADJ>(a, wi, sbuf, int(threadIdx.x));
 }
 
 // ---------------------------------------------------------------------------
 // A1: radial transform of two sinogram rows
 // ---------------------------------------------------------------------------
-
-// Filtered back-projection weight of half-line index j of an L-point line:
-// (pi/n_angles) |k| B(k) with k = j/L cycles per pixel and B = 1 (ramp) or
-// 1/(1 + (k/cutoff)^(2 order)) (Butterworth).
-template <class LA>
-__device__ __forceinline__ float fbp_weight(const LA& a, int j, int L, int n_angles) {
-  const float k = float(j) / float(L);
-  float w = k;
-  if (a.fbp_filter == 1) {
-    const float x = k * a.fbp_inv_cutoff, x2 = x * x;
-    float pw = 1.f;
-    for (int i = 0; i < a.fbp_order; ++i) pw *= x2;
-    w = k / (1.f + pw);
-  }
-  return w * (3.14159265358979f / float(n_angles));
-}
 
 template <int L, int T, class LA>
 __device__ __forceinline__ void adj_radial_unit(const LA& a, const WorkItem wi, float2* sbuf, const int tid) {
@@ -812,23 +847,7 @@ __device__ __forceinline__ void adj_radial_unit(const LA& a, const WorkItem wi, 
   }
   __syncthreads();
   fft_lds<L, T, false>(s, d.tw_Nt, tid);
-  const int H = L / 2 + 1;
-  NR_G float2* __restrict__ o0 = d.yh + size_t(a0) * H;
-  const float inv = 1.0f / float(L);
-  NR_STRIDED(j, H, T) {
-    const float2 z1 = s[j], z2 = s[j == 0 ? 0 : L - j];
-    float w = (j == 0 || j == L / 2) ? inv : 2.0f * inv;
-    if (a.fbp_filter >= 0) w *= fbp_weight(a, j, L, d.na);
-    float2 A = make_float2(0.5f * w * (z1.x + z2.x), 0.5f * w * (z1.y - z2.y));
-    float2 B = make_float2(0.5f * w * (z1.y + z2.y), 0.5f * w * (z2.x - z1.x));
-    if (d.shift) {   // transpose of the forward's phase
-      const float2 q = c_conj(d.shift[j]);
-      A = c_mul(A, q);
-      B = c_mul(B, q);
-    }
-    o0[j] = A;
-    if (has1) o0[H + j] = B;
-  }
+  store_half_lines<L, T>(a, d, a0, has1, s, tid);
   __syncthreads();
 }
 
@@ -1362,7 +1381,7 @@ __device__ __forceinline__ void persist_unit(const LA& a, const KB& kb, int stag
     }
     case StageKind::FwdRadial:
       switch (L) {
-#define NR_CASE(l) case l: fwd_radial_unit<l, T>(a, wi, f2, tid); return;
+#define NR_CASE(l) case l: fwd_radial_unit<l, T, false>(a, wi, f2, tid); return;
         NR_PERSIST_LENGTHS(NR_CASE)
 #undef NR_CASE
       }
@@ -1572,7 +1591,10 @@ hipError_t launch_stage(StageKind stage, int L, const LaunchArgs& a, const KBArg
       break;
     case StageKind::FwdRadial:
       switch (L) {
-#define NR_CASE(l) case l: return launch(k_fwd_radial<l>, fft_threads(l), a.n_work, st, a);
+#define NR_CASE(l)                                                                       \
+  case l:                                                                                \
+    return a.radial_adjoint ? launch(k_fwd_radial<l, true>, fft_threads(l), a.n_work, st, a) \
+                            : launch(k_fwd_radial<l, false>, fft_threads(l), a.n_work, st, a);
         NR_LENGTHS(NR_CASE)
 #undef NR_CASE
       }

@@ -22,6 +22,7 @@ struct LaunchArgs {
   int fbp_order;
   float fbp_inv_cutoff;
   int stream_stores;        // 1: the forward columns and the spreading store their rows non-temporally
+  int radial_adjoint;       // 1: the forward radial stage also runs the adjoint's (A1) on the rows it stores
   int pair_units;           // set by launch_stage: 1 when workgroups run two units each (columns, tile items)
 };
 

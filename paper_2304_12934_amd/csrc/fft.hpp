@@ -51,7 +51,26 @@ constexpr int pow2_exponent(int v) {
   return e;
 }
 
+// A transform is named by its length, plus kAdjointPlan for the adjoint's
+// radices: 640 = 8 8 10 and 16 16 L/256 from 1024 to 2560 points, three passes
+// through LDS where the general plan takes four.  Columns and rows in us per
+// slice, four passes and three: 2560 10.0 + 6.4 and 8.8 + 6.1, 2048 6.9 + 3.5
+// and 6.4 + 3.4, 1280 3.1 + 2.3 and 2.8 + 2.0, 1024 1.85 + 1.2 and 1.63 + 1.1,
+// 640 1.75 + 1.17 and 1.62 + 1.12.  Shorter ones have too few butterflies of
+// such a radix for a wavefront.  The forward keeps the general plan and its
+// roundings.
+constexpr int kAdjointPlan = 1 << 20;
+constexpr int fft_len(int L) { return L & (kAdjointPlan - 1); }
+constexpr bool adjoint_plan_differs(int L) { return L == 640 || L == 1024 || L == 1280 || L == 2048 || L == 2560; }
+
 constexpr int radix_of(int L, int p) {
+  if (L & kAdjointPlan) {
+    L = fft_len(L);
+    if (adjoint_plan_differs(L)) {
+      const int first = L == 640 ? 8 : 16;
+      return p < 2 ? first : (p == 2 ? L / (first * first) : 1);
+    }
+  }
   // three passes for the two longest transforms of the 2560^2 and 2048^2
   // workloads: radix 16 and 20 butterflies in registers, one LDS round trip
   // per pass
@@ -99,7 +118,7 @@ constexpr int span_before(int L, int p) {
   return s;
 }
 
-constexpr bool radix_plan_complete(int L) { return span_before(L, num_passes(L)) == L; }
+constexpr bool radix_plan_complete(int L) { return span_before(L, num_passes(L)) == fft_len(L); }
 
 // ---------------------------------------------------------------------------
 // small DFTs, X_k = sum_n x_n exp(-+2 pi i n k / R)
@@ -221,6 +240,15 @@ struct UnitRoots<16> {
                                   -1.f, -0.92387953251128674f, -0.70710678118654757f, -0.38268343236508984f};
 };
 template <>
+struct UnitRoots<10> {
+  static constexpr float c[10] = {1.f, 0.80901699437494742f, 0.30901699437494742f, -0.30901699437494742f,
+                                  -0.80901699437494742f, -1.f, -0.80901699437494742f, -0.30901699437494742f,
+                                  0.30901699437494742f, 0.80901699437494742f};
+  static constexpr float s[10] = {0.f, 0.58778525229247313f, 0.95105651629515357f, 0.95105651629515357f,
+                                  0.58778525229247313f, 0.f, -0.58778525229247313f, -0.95105651629515357f,
+                                  -0.95105651629515357f, -0.58778525229247313f};
+};
+template <>
 struct UnitRoots<20> {
   static constexpr float c[20] = {1.f, 0.95105651629515357f, 0.80901699437494742f, 0.58778525229247313f,
                                   0.30901699437494742f, 0.f, -0.30901699437494742f, -0.58778525229247313f,
@@ -281,6 +309,8 @@ struct DftPQ {
 template <bool INV, bool HALF>
 struct Dft<16, INV, HALF> : DftPQ<4, 4, INV, HALF> {};
 template <bool INV>
+struct Dft<10, INV> : DftPQ<5, 2, INV> {};
+template <bool INV>
 struct Dft<20, INV> : DftPQ<5, 4, INV> {};
 
 // ---------------------------------------------------------------------------
@@ -296,7 +326,7 @@ struct Dft<20, INV> : DftPQ<5, 4, INV> {};
 
 template <int L>
 constexpr int lds_elems() {
-  return L;
+  return fft_len(L);
 }
 
 struct Lds {
@@ -379,7 +409,7 @@ template <int L, int T, int P, bool INV>
 __device__ __forceinline__ void fft_pass(Lds s, TwPtr __restrict__ tw, int tid) {
   constexpr int R = radix_of(L, P);
   constexpr int Ns = span_before(L, P);
-  constexpr int NB = L / R;
+  constexpr int NB = fft_len(L) / R;
   constexpr int PER = (NB + T - 1) / T;
   float2 v[PER][R];
   float2 w[PER][R - 1];
@@ -390,7 +420,7 @@ __device__ __forceinline__ void fft_pass(Lds s, TwPtr __restrict__ tw, int tid) 
     for (int i = 0; i < PER; ++i) {
       const int j = (NB % T == 0 || tid + i * T < NB) ? tid + i * T : 0;
       const int k = j % Ns;
-      radix_twiddles<R>(tw, k * (L / (Ns * R)), w[i]);
+      radix_twiddles<R>(tw, k * (fft_len(L) / (Ns * R)), w[i]);
     }
   }
 #pragma unroll
@@ -415,7 +445,7 @@ __device__ __forceinline__ void fft_pass(Lds s, TwPtr __restrict__ tw, int tid) 
       // base = k mod Ns below r Ns, a multiple of Ns R above it (0 in the last pass)
       const int base = (j - k) * R + k;
 #pragma unroll
-      for (int r = 0; r < R; ++r) butterfly_elem<Ns, is_pow2(Ns) && (is_pow2(R) || Ns * R == L)>(s, base, r) = v[i][r];
+      for (int r = 0; r < R; ++r) butterfly_elem<Ns, is_pow2(Ns) && (is_pow2(R) || Ns * R == fft_len(L))>(s, base, r) = v[i][r];
     }
   }
   __syncthreads();
@@ -442,7 +472,7 @@ __device__ __forceinline__ void fft_lds(Lds s, TwPtr __restrict__ tw, int tid) {
 // A thread's butterflies of pass P in registers.
 template <int L, int T, int P>
 struct Regs {
-  static constexpr int R = radix_of(L, P), NB = L / R, PER = (NB + T - 1) / T;
+  static constexpr int R = radix_of(L, P), NB = fft_len(L) / R, PER = (NB + T - 1) / T;
   float2 v[PER][R];
 };
 
@@ -457,7 +487,7 @@ struct Regs {
 // Inputs of the first pass in registers.
 template <int L, int T, class Load>
 __device__ __forceinline__ void first_inputs(Regs<L, T, 0>& a, int tid, Load&& load) {
-  constexpr int R = radix_of(L, 0), NB = L / R;
+  constexpr int R = radix_of(L, 0), NB = fft_len(L) / R;
 #pragma unroll
   for (int i = 0; i < Regs<L, T, 0>::PER; ++i) {
     const int j = tid + i * T;
@@ -471,7 +501,7 @@ __device__ __forceinline__ void first_inputs(Regs<L, T, 0>& a, int tid, Load&& l
 // The first pass of the inputs in a, written to the LDS buffer.
 template <int L, int T, bool INV>
 __device__ __forceinline__ void first_pass_to_lds(Lds s, int tid, Regs<L, T, 0>& a) {
-  constexpr int R = radix_of(L, 0), NB = L / R;
+  constexpr int R = radix_of(L, 0), NB = fft_len(L) / R;
 #pragma unroll
   for (int i = 0; i < Regs<L, T, 0>::PER; ++i) {
     const int j = tid + i * T;
@@ -488,8 +518,8 @@ __device__ __forceinline__ void first_pass_to_lds(Lds s, int tid, Regs<L, T, 0>&
 // product is then fused into them.
 template <int L, int T, bool INV, bool HALF, class Load>
 __device__ __forceinline__ void fft_first_pass_from(Lds s, int tid, Load&& load) {
-  constexpr int R = radix_of(L, 0), NB = L / R;
-  static_assert(!HALF || (R % 4 == 0 && L % 4 == 0), "the first radix must split the zero padding evenly");
+  constexpr int R = radix_of(L, 0), NB = fft_len(L) / R;
+  static_assert(!HALF || (R % 4 == 0 && fft_len(L) % 4 == 0), "the first radix must split the zero padding evenly");
 #pragma unroll
   for (int i = 0; i < (NB + T - 1) / T; ++i) {
     const int j = tid + i * T;
@@ -527,7 +557,7 @@ __device__ __forceinline__ void store_kept(int j, const float2 (&v)[R], Store&& 
       if (r < R / 4 || r >= R - R / 4) store(j, r, v[r]);
     } else {
       const int n = j + r * NS;
-      if (!HALF || n < L / 4 || n >= L - L / 4) store(j, r, v[r]);
+      if (!HALF || n < fft_len(L) / 4 || n >= fft_len(L) - fft_len(L) / 4) store(j, r, v[r]);
     }
   }
 }
@@ -547,7 +577,7 @@ __device__ __forceinline__ void fft_lds_store_out(Lds s, TwPtr __restrict__ tw, 
   constexpr int P = num_passes(L) - 1;
   constexpr int R = radix_of(L, P);
   constexpr int Ns = span_before(L, P);
-  static_assert(Ns * R == L && P >= 1 && START <= P, "a transform of at least two passes");
+  static_assert(Ns * R == fft_len(L) && P >= 1 && START <= P, "a transform of at least two passes");
   fft_passes<L, T, INV, START, P>(s, tw, tid);
   constexpr int PER = (Ns + T - 1) / T;
 #pragma unroll
@@ -606,8 +636,8 @@ __device__ __forceinline__ float& butterfly_elem(LdsF s, int base, int r) {
 // outputs of pass P (in a) -> inputs of pass P + 1 (in u)
 template <int L, int T, int P>
 __device__ __forceinline__ void split_exchange(LdsF s, int tid, const Regs<L, T, P>& a, Regs<L, T, P + 1>& u) {
-  constexpr int R = radix_of(L, P), Ns = span_before(L, P), NB = L / R;
-  constexpr int R1 = radix_of(L, P + 1), NB1 = L / R1;
+  constexpr int R = radix_of(L, P), Ns = span_before(L, P), NB = fft_len(L) / R;
+  constexpr int R1 = radix_of(L, P + 1), NB1 = fft_len(L) / R1;
 #pragma unroll
   for (int part = 0; part < 2; ++part) {
     if (part) __syncthreads();
@@ -619,7 +649,7 @@ __device__ __forceinline__ void split_exchange(LdsF s, int tid, const Regs<L, T,
         const int base = (j - k) * R + k;
 #pragma unroll
         for (int r = 0; r < R; ++r)
-          butterfly_elem<Ns, is_pow2(Ns) && (is_pow2(R) || Ns * R == L)>(s, base, r) = part ? a.v[i][r].y : a.v[i][r].x;
+          butterfly_elem<Ns, is_pow2(Ns) && (is_pow2(R) || Ns * R == fft_len(L))>(s, base, r) = part ? a.v[i][r].y : a.v[i][r].x;
       }
     }
     __syncthreads();
@@ -643,7 +673,7 @@ __device__ __forceinline__ void split_exchange(LdsF s, int tid, const Regs<L, T,
 template <int L, int T, int P, bool INV, bool HALF, class Store>
 __device__ __forceinline__ void split_passes(LdsF s, TwPtr __restrict__ tw, int tid, const Regs<L, T, P - 1>& a,
                                              Store&& store) {
-  constexpr int R = radix_of(L, P), Ns = span_before(L, P), NB = L / R;
+  constexpr int R = radix_of(L, P), Ns = span_before(L, P), NB = fft_len(L) / R;
   Regs<L, T, P> u;
   split_exchange<L, T, P - 1>(s, tid, a, u);
 #pragma unroll
@@ -652,7 +682,7 @@ __device__ __forceinline__ void split_passes(LdsF s, TwPtr __restrict__ tw, int 
     if (NB % T == 0 || j < NB) {
       const int k = j % Ns;
       float2 w[R - 1];
-      radix_twiddles<R>(tw, k * (L / (Ns * R)), w);
+      radix_twiddles<R>(tw, k * (fft_len(L) / (Ns * R)), w);
 #pragma unroll
       for (int r = 1; r < R; ++r) u.v[i][r] = c_mul(u.v[i][r], INV ? c_conj(w[r - 1]) : w[r - 1]);
       Dft<R, INV>::run(u.v[i]);
@@ -682,7 +712,7 @@ __device__ __forceinline__ void fft_store_out(float2* lds, TwPtr __restrict__ tw
 }
 template <int L, bool SPLIT>
 constexpr int store_out_lds_elems() {
-  return SPLIT ? L / 2 : lds_elems<L>();
+  return SPLIT ? fft_len(L) / 2 : lds_elems<L>();
 }
 
 // threads per transform for a length-L FFT.  For 5·2^a lengths five
@@ -692,5 +722,9 @@ constexpr int store_out_lds_elems() {
 constexpr int fft_threads(int L) {
   return (L == 2560 || L == 5120) ? 320 : (L >= 2048 ? 256 : (L >= 512 ? 128 : 64));
 }
+
+// threads per transform of the adjoint's grid transforms: one or two of its
+// wider butterflies a thread and pass
+constexpr int adj_threads(int L) { return L == 1024 ? 64 : (L == 2048 ? 128 : (L == 2560 ? 256 : fft_threads(L))); }
 
 }  // namespace nrk

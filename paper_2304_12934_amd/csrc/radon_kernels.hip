@@ -1199,9 +1199,9 @@ template <int L>
 __device__ __forceinline__ Rsrc disc_cells(const NR_G float2* row, int colpad, int lim) {
   return buf(row + colpad + L / 2 - max(lim, 0), 8u * uint32_t(max(2 * lim + 1, 0)));
 }
-template <int L>
+template <int P>
 __device__ __forceinline__ float2 disc_cell(Rsrc disc, int lim, int j, int r) {
-  constexpr int R = radix_of(L, 0);
+  constexpr int L = fft_len(P), R = radix_of(P, 0);
   static_assert(R % 2 == 0, "q_y changes sign between two inputs of a butterfly");
   const int qy = j + r * (L / R) - (r < R / 2 ? 0 : L);
   return buf_load<float2>(disc, 8u * uint32_t(qy + lim), 0u);
@@ -1228,10 +1228,11 @@ __device__ __forceinline__ void adj_cols_unit(const LA& a, const WorkItem wi, fl
   // column whose disc stops short of them, and that has no mirror rows (all
   // but a few), reads each cell once.
   const int lim = r2 < 0 ? -1 : int(sqrtf(float(r2)));
-  Regs<L, T, 0> in;
+  constexpr int P = L | kAdjointPlan;
+  Regs<P, T, 0> in;
   if (m1 || m2 || lim >= L / 2 - colpad) {
-    first_inputs<L, T>(in, tid, [&](int j, int r) {
-      const int n = j + r * (L / radix_of(L, 0));
+    first_inputs<P, T>(in, tid, [&](int j, int r) {
+      const int n = j + r * (L / radix_of(P, 0));
       const int qy = n < L / 2 ? n : n - L;
       if (qy * qy > r2) return make_float2(0.f, 0.f);
       float2 v = load_folded<L>(row, colpad, n);
@@ -1242,13 +1243,13 @@ __device__ __forceinline__ void adj_cols_unit(const LA& a, const WorkItem wi, fl
     });
   } else {
     const Rsrc disc = disc_cells<L>(row, colpad, lim);
-    first_inputs<L, T>(in, tid, [&](int j, int r) { return disc_cell<L>(disc, lim, j, r); });
+    first_inputs<P, T>(in, tid, [&](int j, int r) { return disc_cell<P>(disc, lim, j, r); });
   }
   // only y = iy - N/2 in [-N/2, N/2) is kept: natural indices [0, N/2) and
   // [L - N/2, L); row iy of column qx is half iy & 1 of tile entry t4(qx, iy / 2)
   const Rsrc Tq = buf((const NR_G float4*)d.T + t4(qx, 0, N), 32u * N);
-  fft_store_out<L, T, true, SPLIT>(sbuf, d.tw_G, tid, in, [&](int j, int r, float2 v) {
-    constexpr int Ns = L / radix_of(L, num_passes(L) - 1);
+  fft_store_out<P, T, true, SPLIT>(sbuf, d.tw_G, tid, in, [&](int j, int r, float2 v) {
+    constexpr int Ns = L / radix_of(P, num_passes(P) - 1);
     const int c = r * Ns + (r * Ns < L / 2 ? N / 2 : N / 2 - L);   // row iy = j + c, c even
     static_assert(Ns % 2 == 0, "row pairs");
     // (c < 0, where a radix splits the kept outputs unevenly, goes into the lane's offset)
@@ -1259,15 +1260,16 @@ __device__ __forceinline__ void adj_cols_unit(const LA& a, const WorkItem wi, fl
 }
 
 // wavefronts per SIMD the adjoint transforms are compiled for: with the split
-// exchange six (80 VGPRs; seven spill a few at L = 5120 and ran slower)
-constexpr int store_out_waves(int L) { return split_exchange_length(L) ? 6 : 1; }
+// exchange six (80 VGPRs; seven spill a few at L = 5120 and ran slower), with
+// the three-pass plans seven (72)
+constexpr int store_out_waves(int L) { return split_exchange_length(L) ? 6 : (adjoint_plan_differs(L) ? 7 : 1); }
 
 template <int L>
-__global__ __launch_bounds__(fft_threads(L)) __attribute__((amdgpu_waves_per_eu(store_out_waves(L)))) void k_adj_cols(
+__global__ __launch_bounds__(adj_threads(L)) __attribute__((amdgpu_waves_per_eu(store_out_waves(L)))) void k_adj_cols(
     LaunchArgs a) {
   constexpr bool SPLIT = split_exchange_length(L);
   __shared__ float2 sbuf[store_out_lds_elems<L, SPLIT>()];
-  NR_FOR_EACH_UNIT(a, wi) adj_cols_unit<L, fft_threads(L), SPLIT>(a, wi, sbuf, int(threadIdx.x));
+  NR_FOR_EACH_UNIT(a, wi) adj_cols_unit<L, adj_threads(L), SPLIT>(a, wi, sbuf, int(threadIdx.x));
 }
 
 // ---------------------------------------------------------------------------
@@ -1283,9 +1285,10 @@ __device__ __forceinline__ void adj_rows_unit(const LA& a, const WorkItem wi, fl
   // Hermitian completion with doubled real parts at q = 0 and G/2, two rows
   // packed: index n <= L/2 takes entry q = n as X + iY, index L - q the
   // conjugate-symmetric combination of the same entry
-  Regs<L, T, 0> cells;
-  first_inputs<L, T>(cells, tid, [&](int j, int r) {
-    constexpr int R = radix_of(L, 0), NB = L / R;
+  constexpr int P = L | kAdjointPlan;
+  Regs<P, T, 0> cells;
+  first_inputs<P, T>(cells, tid, [&](int j, int r) {
+    constexpr int R = radix_of(P, 0), NB = L / R;
     static_assert(NB % 4 == 0 && R % 2 == 0, "whole tiles of T per input");
     // r < R/2: q = n = j + r NB; else q = L - n = (NB - j) + (R - 1 - r) NB
     const bool low = r < R / 2;
@@ -1303,8 +1306,8 @@ __device__ __forceinline__ void adj_rows_unit(const LA& a, const WorkItem wi, fl
   const Rsrc g = buf((NR_G float*)a.vol_out + d.vol_off + size_t(iy0) * N, 8u * N);
   const Rsrc dp = buf(d.deapod, 4u * N);
   // x = ix - N/2 in [-N/2, N/2) is kept: natural indices [0, N/2) and [L - N/2, L)
-  fft_store_out<L, T, true, SPLIT>(sbuf, d.tw_G, tid, cells, [&](int j, int r, float2 z) {
-    constexpr int Ns = L / radix_of(L, num_passes(L) - 1);
+  fft_store_out<P, T, true, SPLIT>(sbuf, d.tw_G, tid, cells, [&](int j, int r, float2 z) {
+    constexpr int Ns = L / radix_of(P, num_passes(P) - 1);
     const int ix0 = r * Ns + (r * Ns < L / 2 ? N / 2 : N / 2 - L);   // ix = j + ix0
     const uint32_t jo = 4u * uint32_t(ix0 < 0 ? j + ix0 : j), c = 4u * uint32_t(max(ix0, 0));
     const float dx = buf_load<float>(dp, jo, c);
@@ -1315,11 +1318,11 @@ __device__ __forceinline__ void adj_rows_unit(const LA& a, const WorkItem wi, fl
 }
 
 template <int L>
-__global__ __launch_bounds__(fft_threads(L)) __attribute__((amdgpu_waves_per_eu(store_out_waves(L)))) void k_adj_rows(
+__global__ __launch_bounds__(adj_threads(L)) __attribute__((amdgpu_waves_per_eu(store_out_waves(L)))) void k_adj_rows(
     LaunchArgs a) {
   constexpr bool SPLIT = split_exchange_length(L);
   __shared__ float2 sbuf[store_out_lds_elems<L, SPLIT>()];
-  NR_FOR_EACH_UNIT(a, wi) adj_rows_unit<L, fft_threads(L), SPLIT>(a, wi, sbuf, int(threadIdx.x));
+  NR_FOR_EACH_UNIT(a, wi) adj_rows_unit<L, adj_threads(L), SPLIT>(a, wi, sbuf, int(threadIdx.x));
 }
 
 // ---------------------------------------------------------------------------
@@ -1615,14 +1618,14 @@ hipError_t launch_stage(StageKind stage, int L, const LaunchArgs& a, const KBArg
     }
     case StageKind::AdjCols:
       switch (L) {
-#define NR_CASE(l) case l: return launch(k_adj_cols<l>, fft_threads(l), a.n_work, st, a);
+#define NR_CASE(l) case l: return launch(k_adj_cols<l>, adj_threads(l), a.n_work, st, a);
         NR_LENGTHS(NR_CASE)
 #undef NR_CASE
       }
       break;
     case StageKind::AdjRows:
       switch (L) {
-#define NR_CASE(l) case l: return launch(k_adj_rows<l>, fft_threads(l), a.n_work, st, a);
+#define NR_CASE(l) case l: return launch(k_adj_rows<l>, adj_threads(l), a.n_work, st, a);
         NR_LENGTHS(NR_CASE)
 #undef NR_CASE
       }

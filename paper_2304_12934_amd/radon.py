@@ -448,12 +448,17 @@ def qggmrf_grad(vol: torch.Tensor, prior: Prior, scale: float = 1.0, grad: torch
     if grad is None:
         grad = torch.zeros_like(vol)
     _require(grad, vol.numel(), vol.device, "grad")
-    val = torch.zeros(1, dtype=torch.float64, device=vol.device) if value else None
+    val = torch.empty(1, dtype=torch.float64, device=vol.device) if value else None   # the library sets it
+    _qggmrf_into(vol, prior, scale, grad, val)
+    return grad, val
+
+
+def _qggmrf_into(vol: torch.Tensor, prior: Prior, scale: float, grad: torch.Tensor, val: torch.Tensor | None) -> None:
     pr = prior.as_c()
     with torch.cuda.device(vol.device):
         check(lib().qggmrf_grad(_ptr(vol), vol.shape[0], vol.shape[1], ctypes.byref(pr), float(scale),
-                                _ptr(grad), _ptr(val) if value else None, _stream(vol.device)), "qggmrf_grad")
-    return grad, (val if value else None)
+                                _ptr(grad), _ptr(val) if val is not None else None, _stream(vol.device)),
+              "qggmrf_grad")
 
 
 # --------------------------------------------------------------------------
@@ -483,21 +488,23 @@ class DataFidelityFn(torch.autograd.Function):
         xc = x.contiguous()
         _require(xc, plan.vol_numel, plan.device, "x")
         r = torch.empty(plan.sino_shape(), dtype=torch.float32, device=plan.device)
-        val = torch.empty(1, dtype=torch.float64, device=plan.device)
+        val = torch.empty((), dtype=torch.float64, device=plan.device)
         with torch.cuda.device(plan.device):
             check(lib().radon_residual(plan._h, _ptr(xc), _ptr(b), _ptr(r), _ptr(val), _stream(plan.device)),
                   "radon_residual")
         ctx.plan = plan
         ctx.save_for_backward(r)
-        return val[0]
+        return val
 
     @staticmethod
     def backward(ctx, g: torch.Tensor):
         (r,) = ctx.saved_tensors
         grad = ctx.plan.adj(r)
         # scaled on the device whatever g is: testing g == 1 would stall the
-        # host until the forward has finished
-        return grad.mul_(g.to(grad.dtype)), None, None
+        # host until the forward has finished.  The product rounds the float64
+        # scalar g to float32 by itself: a cast of its own is a launch more
+        # (10 us of host time with it, 4.5 without).
+        return grad.mul_(g), None, None
 
 
 class QGGMRFFn(torch.autograd.Function):
@@ -505,14 +512,20 @@ class QGGMRFFn(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, x: torch.Tensor, prior: Prior) -> torch.Tensor:
-        grad, val = qggmrf_grad(x.contiguous(), prior, 1.0, None, value=True)
+        if x.dim() != 3 or x.shape[1] != x.shape[2]:
+            raise ValueError("vol must be [Z, N, N]")
+        xc = x.contiguous()
+        _require(xc, xc.numel(), xc.device, "vol")
+        grad = torch.zeros_like(xc)
+        val = torch.empty((), dtype=torch.float64, device=xc.device)
+        _qggmrf_into(xc, prior, 1.0, grad, val)
         ctx.save_for_backward(grad)
-        return val[0]
+        return val
 
     @staticmethod
     def backward(ctx, g: torch.Tensor):
         (grad,) = ctx.saved_tensors
-        return grad * g.to(grad.dtype), None
+        return grad * g, None   # float32: g is a float64 scalar
 
 
 # --------------------------------------------------------------------------

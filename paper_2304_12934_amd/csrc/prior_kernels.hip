@@ -325,10 +325,12 @@ __global__ void k_set_double(double* p, double v) { *p = v; }
 // taken one by one.  The sums are formed in float64 per thread, then over the
 // wavefront, the workgroup and, by one atomic per workgroup, the grid, whose
 // size follows the element count (2048 workgroups whatever the count spent
-// 27 us on their atomics alone).  The MBIR update (restart test and update, 44
-// bytes per voxel), against one element per thread and fixed grids: 32 x
-// 1280^2 453 -> 431 us (5.36 TB/s), 16 x 512^2 59.7 -> 45.6, 4 x 128^2
-// 36.5 -> 13.5.
+// 27 us on their atomics alone).  The MBIR update (step with restart test, then
+// extrapolation, 40 bytes per voxel), against one element per thread, fixed
+// grids and 44 bytes: 32 x 1280^2 453 -> 402 us (5.2 TB/s), 16 x 512^2 59.7 ->
+// 41, 4 x 128^2 36.5 -> 13.5.  The step pass reads four streams, writes three
+// and is best with few workgroups (768; with 1536 421 and 48 us, 2048 415
+// and 51).
 // ---------------------------------------------------------------------------
 
 template <int V>
@@ -394,13 +396,18 @@ unsigned pass_blocks(size_t count, int v, size_t most) {
 // <g, x' - x> with x' = y - g/L (clamped at 0 when nonneg); non-finite flag.
 // With cand, x' is also stored there (the monotone step evaluates it).  With
 // gp, the gradient is g + gp (a second part computed elsewhere), stored back
-// into g.
+// into g.  STEP: the step is taken, x_prev <- x and x <- x' (gp may be x_prev:
+// an element is read before it is replaced), so that the pass after the
+// momentum is known reads x and x_prev alone: 40 bytes per voxel for the two
+// instead of 44 where that pass formed x' a second time.
+template <bool STEP>
 struct MbirDot {
-  const float *x, *y;
+  float* x;
+  const float* y;
   float* g;
   float inv_L;
   int nonneg;
-  float* cand;
+  float* cand;   // STEP: x_prev
   const float* gp;
   double acc;
   int bad;
@@ -421,17 +428,22 @@ struct MbirDot {
       acc += double(gi.v[e]) * double(xn.v[e] - xi.v[e]);
       if (!isfinite(gi.v[e]) || !isfinite(xn.v[e])) bad = 1;
     }
-    if (cand) vstore<V>(cand, i, xn);
+    if (STEP) {
+      vstore<V>(cand, i, xi);
+      vstore<V>(x, i, xn);
+    } else if (cand) {
+      vstore<V>(cand, i, xn);
+    }
   }
 };
 
-template <int V>
-__global__ __launch_bounds__(256) void k_mbir_dot(const float* x, const float* y, float* g, size_t count, float inv_L,
+template <int V, bool STEP>
+__global__ __launch_bounds__(256) void k_mbir_dot(float* x, const float* y, float* g, size_t count, float inv_L,
                                                   int nonneg, double* state, float* cand, const float* gp) {
   __shared__ double red[4];
   __shared__ int bad;
   if (threadIdx.x == 0) bad = 0;
-  MbirDot body{x, y, g, inv_L, nonneg, cand, gp, 0.0, 0};
+  MbirDot<STEP> body{x, y, g, inv_L, nonneg, cand, gp, 0.0, 0};
   for_each_group<V, false>(count, body);
   __syncthreads();
   if (body.bad) bad = 1;
@@ -470,32 +482,28 @@ __global__ void k_mbir_finalize(double* state, int restart, int monotone) {
   state[kStAccepted] = accept;
 }
 
-// x' = y - g/L; y <- x' + beta (x' - x); x_prev <- x; x <- x'
-struct MbirUpdate {
-  float *x, *x_prev, *y;
-  const float* g;
-  float inv_L, beta;
-  int nonneg;
+// y = x + beta (x - x_prev) with the beta of the last finalised step: the
+// extrapolated point of the accelerated-gradient iteration, after the pass
+// that took the step, or formed when the iterates live elsewhere (host memory)
+// and only x and x_prev are kept
+struct MbirExtrapolate {
+  float* y;
+  const float *x, *x_prev;
+  float beta;
   template <int V>
   __device__ __forceinline__ void operator()(size_t i) const {
-    const Vec<V> gi = vload<V>(g, i), xo = vload<V>(x, i);
-    Vec<V> yi = vload<V>(y, i), xn;
+    const Vec<V> xn = vload<V>(x, i), xo = vload<V>(x_prev, i);
+    Vec<V> yi;
 #pragma unroll
-    for (int e = 0; e < V; ++e) {
-      xn.v[e] = yi.v[e] - inv_L * gi.v[e];
-      if (nonneg) xn.v[e] = fmaxf(xn.v[e], 0.f);
-      yi.v[e] = xn.v[e] + beta * (xn.v[e] - xo.v[e]);
-    }
+    for (int e = 0; e < V; ++e) yi.v[e] = xn.v[e] + beta * (xn.v[e] - xo.v[e]);
     vstore<V>(y, i, yi);
-    vstore<V>(x_prev, i, xo);
-    vstore<V>(x, i, xn);
   }
 };
 
 template <int V>
-__global__ __launch_bounds__(256) void k_mbir_update(float* x, float* x_prev, float* y, const float* g, size_t count,
-                                                     float inv_L, int nonneg, const double* __restrict__ state) {
-  for_each_group<V, true>(count, MbirUpdate{x, x_prev, y, g, inv_L, float(state[kStBeta]), nonneg});
+__global__ __launch_bounds__(256) void k_mbir_extrapolate(float* y, const float* x, const float* x_prev, size_t count,
+                                                          const double* __restrict__ state) {
+  for_each_group<V, true>(count, MbirExtrapolate{y, x, x_prev, float(state[kStBeta])});
 }
 
 // Monotone update, the candidate x' held in x_prev: accepted, x <- x',
@@ -623,36 +631,43 @@ hipError_t launch_qggmrf(const float* f, float* grad, double* value, int nz, int
   return hipGetLastError();
 }
 
-static hipError_t mbir_dot(const float* x, const float* y, float* g, size_t count, float inv_L, int nonneg, double* state,
+template <bool STEP>
+static hipError_t mbir_dot(float* x, const float* y, float* g, size_t count, float inv_L, int nonneg, double* state,
                            float* cand, const float* gp, hipStream_t st) {
   if (on_16_bytes(x, y, g, cand, gp))
-    hipLaunchKernelGGL(k_mbir_dot<4>, dim3(pass_blocks(count, 4, 768)), dim3(256), 0, st, x, y, g, count, inv_L, nonneg,
-                       state, cand, gp);
+    hipLaunchKernelGGL((k_mbir_dot<4, STEP>), dim3(pass_blocks(count, 4, 768)), dim3(256), 0, st, x, y, g, count, inv_L,
+                       nonneg, state, cand, gp);
   else
-    hipLaunchKernelGGL(k_mbir_dot<1>, dim3(pass_blocks(count, 1, 768)), dim3(256), 0, st, x, y, g, count, inv_L, nonneg,
-                       state, cand, gp);
+    hipLaunchKernelGGL((k_mbir_dot<1, STEP>), dim3(pass_blocks(count, 1, 768)), dim3(256), 0, st, x, y, g, count, inv_L,
+                       nonneg, state, cand, gp);
+  return hipGetLastError();
+}
+
+hipError_t launch_mbir_extrapolate(float* y, const float* x, const float* x_prev, size_t count, const double* state,
+                                   hipStream_t st) {
+  if (on_16_bytes(y, x, x_prev))
+    hipLaunchKernelGGL(k_mbir_extrapolate<4>, dim3(pass_blocks(count, 4, 8192)), dim3(256), 0, st, y, x, x_prev, count,
+                       state);
+  else
+    hipLaunchKernelGGL(k_mbir_extrapolate<1>, dim3(pass_blocks(count, 1, 8192)), dim3(256), 0, st, y, x, x_prev, count,
+                       state);
   return hipGetLastError();
 }
 
 hipError_t launch_mbir_update(float* x, float* x_prev, float* y, float* g, size_t count, float inv_L,
                               int nonneg, int restart, double* state, hipStream_t st, bool add_x_prev) {
   hipLaunchKernelGGL(k_set_double, dim3(1), dim3(1), 0, st, state + kStDot, 0.0);
-  if (const hipError_t e = mbir_dot(x, y, g, count, inv_L, nonneg, state, nullptr, add_x_prev ? x_prev : nullptr, st))
+  if (const hipError_t e = mbir_dot<true>(x, y, g, count, inv_L, nonneg, state, x_prev, add_x_prev ? x_prev : nullptr, st))
     return e;
   hipLaunchKernelGGL(k_mbir_finalize, dim3(1), dim3(1), 0, st, state, restart, 0);
-  if (on_16_bytes(x, x_prev, y, g))
-    hipLaunchKernelGGL(k_mbir_update<4>, dim3(pass_blocks(count, 4, 8192)), dim3(256), 0, st, x, x_prev, y, g, count,
-                       inv_L, nonneg, state);
-  else
-    hipLaunchKernelGGL(k_mbir_update<1>, dim3(pass_blocks(count, 1, 8192)), dim3(256), 0, st, x, x_prev, y, g, count,
-                       inv_L, nonneg, state);
-  return hipGetLastError();
+  return launch_mbir_extrapolate(y, x, x_prev, count, state, st);
 }
 
 hipError_t launch_mbir_candidate(const float* x, float* x_prev, const float* y, const float* g, size_t count,
                                  float inv_L, int nonneg, double* state, hipStream_t st) {
   hipLaunchKernelGGL(k_set_double, dim3(1), dim3(1), 0, st, state + kStDot, 0.0);
-  return mbir_dot(x, y, const_cast<float*>(g), count, inv_L, nonneg, state, x_prev, nullptr, st);
+  return mbir_dot<false>(const_cast<float*>(x), y, const_cast<float*>(g), count, inv_L, nonneg, state, x_prev, nullptr,
+                         st);
 }
 
 hipError_t launch_mbir_finish_monotone(float* x, float* x_prev, float* y, size_t count, int restart, double* state,
@@ -663,29 +678,9 @@ hipError_t launch_mbir_finish_monotone(float* x, float* x_prev, float* y, size_t
   return hipGetLastError();
 }
 
-// y = x + beta (x - x_prev) with the beta of the last finalised step: the
-// extrapolated point of the accelerated-gradient iteration, formed when the
-// iterates live elsewhere (host memory) and only x and x_prev are kept
-__global__ __launch_bounds__(256) void k_mbir_extrapolate(float* __restrict__ y, const float* __restrict__ x,
-                                                          const float* __restrict__ x_prev, size_t count,
-                                                          const double* __restrict__ state) {
-  const float beta = float(state[kStBeta]);
-  for (size_t i = size_t(blockIdx.x) * 256 + threadIdx.x; i < count; i += size_t(gridDim.x) * 256) {
-    const float xn = x[i];
-    y[i] = xn + beta * (xn - x_prev[i]);
-  }
-}
-
-hipError_t launch_mbir_extrapolate(float* y, const float* x, const float* x_prev, size_t count, const double* state,
-                                   hipStream_t st) {
-  const size_t blocks = std::min<size_t>(4096, std::max<size_t>(1, (count + 255) / 256));
-  hipLaunchKernelGGL(k_mbir_extrapolate, dim3(unsigned(blocks)), dim3(256), 0, st, y, x, x_prev, count, state);
-  return hipGetLastError();
-}
-
 hipError_t launch_mbir_dot_accumulate(const float* x, const float* y, float* g, const float* gp, size_t count,
                                       float inv_L, int nonneg, double* state, float* cand, hipStream_t st) {
-  return mbir_dot(x, y, g, count, inv_L, nonneg, state, cand, gp, st);
+  return mbir_dot<false>(const_cast<float*>(x), y, g, count, inv_L, nonneg, state, cand, gp, st);
 }
 
 hipError_t launch_mbir_finalize(double* state, int restart, hipStream_t st) {

@@ -441,7 +441,8 @@ nr_status nr_plan_check(nr_plan* plan, nr_stream stream);
  * point entries, info[3] = spreading work items, info[4] = polynomial degree,
  * info[5] = scratch slots (slices per batch), info[6] = batches,
  * info[7] = kernel launches of a forward and an adjoint call (radon_normal,
- * which joins their radial stages, takes one fewer per detector length). */
+ * which joins the radial stages of all but large batches, takes one fewer per
+ * detector length and batch there). */
 nr_status nr_plan_info(const nr_plan* plan, int32_t index, int64_t* info, int32_t count);
 
 #ifdef __cplusplus

@@ -295,8 +295,19 @@ nr_status run_batches(nr_plan* plan, bool fwd, const float* b, bool adj, const f
     const nr::Batch& bt = p.batches[bi];
     hipStream_t bs = lane_stream(bt);
     // a forward whose sinogram is the adjoint's input: the forward's radial
-    // stage runs the adjoint's too (while stages are timed, each on its own)
-    const bool join_radial = fwd && adj && !fbp && sino_in == sino_out && p.tune.interp_mode == 0 && !plan->profiling;
+    // stage runs the adjoint's too (while stages are timed, each on its own).
+    // The joined kernel saves a launch and a read of the rows but keeps 10
+    // wavefronts per CU where the two keep 16, which long stages feel more: us
+    // per radon_normal, joined and not, 128^2 (0.02 M points of radial lines)
+    // 39 and 41, 16 x 512^2 (1.6 M) 179 and 185, 8 x 2048^2 (3.0 M) 817 and
+    // 824, 8 x 1024^2 (3.7 M) 364 and 364, 32 x 1280^2 (5.2 M) 1415 and 1406,
+    // 8 x 2560^2 (10.5 M) 1528 and 1503.
+    constexpr size_t kJoinRadialBelow = size_t(1) << 22;
+    size_t radial_points = 0;
+    for (const nr::StageLaunch& sl : bt.fwd)
+      if (sl.stage == nr::Stage::FwdRadial) radial_points += size_t(sl.n_work) * size_t(sl.L);
+    const bool join_radial = fwd && adj && !fbp && sino_in == sino_out && p.tune.interp_mode == 0 && !plan->profiling &&
+                             radial_points < kJoinRadialBelow;
     std::vector<const nr::StageLaunch*> seq;
     if (fwd)
       for (const nr::StageLaunch& sl : bt.fwd) seq.push_back(&sl);

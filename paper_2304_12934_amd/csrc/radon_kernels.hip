@@ -27,7 +27,9 @@
 //   (F3+F4 k_fwd_interp does both per angle pair, gathering from the grid)
 // Adjoint (Sec. 3, eq. "transpose"): the transpose of every step in reverse:
 //   A1 k_adj_radial  R2C of two sinogram rows, weights c_j/N_t
-//   A2 k_spread_*    WxW spreading onto ext (LDS tiles, or plain atomics)
+//   A2 k_spread_tiles   WxW spreading onto ext, a tile at a time in LDS; the
+//      k_spread_shared  items of a tile that several share leave parts, added
+//                       up here (k_spread_atomic: plain atomics, a cross-check)
 //   A3 k_adj_cols    fold halo cells back, inverse C2C along y, keep N rows
 //   A4 k_adj_rows    inverse half-spectrum transform along x for two rows,
 //                    deapodise, real output

@@ -511,17 +511,26 @@ void append_units_by_cost(std::vector<WorkItem>& out, const std::vector<WorkItem
     for (const auto& r : run) out.push_back(k < r.size() ? r[k] : WorkItem{-1, 0});
 }
 
-// Scratch of one slice: T (its q rows rounded up to a multiple of 4), ext, yh
-// and the parts of its shared tiles, each 256-byte aligned (offsets in bytes).
+// Scratch of one slice: ext, yh, and one area for T (its q rows rounded up to a
+// multiple of 4) and the parts of the shared tiles, each 256-byte aligned
+// (offsets in bytes).  T and the parts never live at the same time: the
+// forward's columns have read T before a spreading starts, and the adjoint's
+// columns write it after the parts are added up, so parts take memory, and a
+// share of a batch's budget, only beyond T's size.  (In an area of their own
+// they cut batches short: sixteen 512^2 slices of 720 angles went from one
+// batch to two and their forward from 104 to 127 us.)
 struct SliceScratch {
-  size_t ext, yh, parts, bytes;
+  size_t yh, T, bytes;
+  size_t grids;   // T, ext and yh alone
 };
 SliceScratch slice_scratch(const Geom& g) {
   SliceScratch o{};
-  o.ext = align_up(size_t((g.G / 2 + 4) / 4 * 4) * g.key.n * sizeof(f2), 256);
-  o.yh = align_up(o.ext + size_t(g.rows) * g.cols * sizeof(f2), 256);
-  o.parts = align_up(o.yh + size_t(g.key.n_angles) * g.H * sizeof(f2), 256);
-  o.bytes = align_up(o.parts + size_t(g.n_parts) * g.tile_w * g.tile_h * sizeof(f2), 256);
+  const size_t t_bytes = size_t((g.G / 2 + 4) / 4 * 4) * g.key.n * sizeof(f2);
+  const size_t part_bytes = size_t(g.n_parts) * g.tile_w * g.tile_h * sizeof(f2);
+  o.yh = align_up(size_t(g.rows) * g.cols * sizeof(f2), 256);
+  o.T = align_up(o.yh + size_t(g.key.n_angles) * g.H * sizeof(f2), 256);
+  o.grids = align_up(o.T + t_bytes, 256);
+  o.bytes = align_up(o.T + std::max(t_bytes, part_bytes), 256);
   return o;
 }
 
@@ -581,15 +590,16 @@ nr_status layout_plan(Plan& plan, std::string& err) {
     size_t used = 0;
     for (int s = b0; s < ns; ++s) {
       const Geom& g = plan.geoms[size_t(plan.slice_geom[size_t(s)])];
-      const size_t need = slice_scratch(g).bytes;
+      const SliceScratch sc = slice_scratch(g);
+      const size_t need = sc.bytes;
       if (!bt.slices.empty() && (used + need > budget || (tu.batch > 0 && int(bt.slices.size()) >= tu.batch)))
         break;
       bt.slices.push_back(s);
       bt.slot_off.push_back(used);
       used += need;
+      bt.bytes += sc.grids;
     }
     b0 += int(bt.slices.size());
-    bt.bytes = used;
     plan.slot_area = std::max(plan.slot_area, used);
     plan.n_slots = std::max(plan.n_slots, int(bt.slices.size()));
     // FFT lengths present in this batch
@@ -848,10 +858,10 @@ std::vector<SliceDesc> slice_descs(const Plan& plan, char* d_ws) {
       d.flip = reinterpret_cast<const int32_t*>(d_ws + g.off_flip);
       char* slot = d_ws + plan.off_slot + size_t(bt.lane) * plan.slot_area + bt.slot_off[k];
       const SliceScratch sc = slice_scratch(g);
-      d.T = reinterpret_cast<float*>(slot);
-      d.ext = reinterpret_cast<float*>(slot + sc.ext);
+      d.ext = reinterpret_cast<float*>(slot);
       d.yh = reinterpret_cast<float*>(slot + sc.yh);
-      d.parts = reinterpret_cast<float*>(slot + sc.parts);
+      d.T = reinterpret_cast<float*>(slot + sc.T);
+      d.parts = d.T;
       d.pts = reinterpret_cast<const int32_t*>(d_ws + g.off_pts);
       d.items = reinterpret_cast<const SpreadItem*>(d_ws + g.off_items);
       d.shared = reinterpret_cast<const SharedTile*>(d_ws + g.off_shared);

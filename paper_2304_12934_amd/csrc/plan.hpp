@@ -120,7 +120,7 @@ constexpr size_t kLastLevelCacheBytes = size_t(256) << 20;
 
 struct Batch {
   int lane = 0;                   // stream (and scratch area) the batch runs on
-  size_t bytes = 0;               // scratch bytes of its slices (T, ext, yh, parts)
+  size_t bytes = 0;               // bytes of its slices' grids (T, ext, yh)
   std::vector<int> slices;
   std::vector<size_t> slot_off;   // scratch offset of each slice inside its lane's slot area
   std::vector<StageLaunch> fwd, adj;

@@ -136,7 +136,10 @@ nr_status nr_plan_destroy(nr_plan* plan);
  *   "tile_w", "tile_h"  spreading tile (64x32 default; 32x32, 64x64, 128x32)
  *   "chunk"             most points per spreading or interpolation work item,
  *                       64..1024
- *                       (1024 default)
+ *                       (1024 default).  The items of a spreading tile cut
+ *                       into several keep their sums in scratch, so small
+ *                       values enlarge the workspace (one 2560^2 slice of
+ *                       1024 angles: 182 MB at 1024, 240 MB at 256, 643 MB at 64)
  *   "interp_mode"       0 = interpolation from LDS-staged grid tiles (every
  *                       point once, by the tile of its first tap) followed by
  *                       the radial transforms (default); 1 = one pass per

@@ -13,6 +13,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "nufftradon.h"
@@ -632,12 +633,13 @@ size_t tune_buffer_bytes(const nr::Plan& p) {
   return 2 * align256(vol_extent(p) * sizeof(float)) + align256(sino_extent(p) * sizeof(float));
 }
 
-// Workspace bytes of the plan under tuning t (lays the plan out for it).
-nr_status layout_bytes(nr_plan* plan, const nr::Tuning& t, size_t& bytes) {
+// Workspace bytes of the plan under tuning t (lays the plan out for it, unless
+// sizes_only).
+nr_status layout_bytes(nr_plan* plan, const nr::Tuning& t, size_t& bytes, bool sizes_only = false) {
   plan->p.tune = t;
   plan->p.laid_out = false;
   std::string err;
-  const nr_status st = nr::layout_plan(plan->p, err);
+  const nr_status st = nr::layout_plan(plan->p, err, sizes_only);
   if (st != NR_OK) return fail(st, err);
   bytes = plan->p.ws_bytes;
   return NR_OK;
@@ -1399,33 +1401,41 @@ nr_status nr_autotune_scratch_bytes(nr_plan* plan, size_t* bytes) {
   if (!plan || !bytes) return fail(NR_INVALID_ARG, "nr_autotune_scratch_bytes: NULL argument");
   const nr::Tuning keep = plan->p.tune;
   const bool was_laid_out = plan->p.laid_out;
-  size_t most = 0, tables = 0, b = 0;
+  // The largest workspace over the search space and the plan's own setting:
+  // slices' scratch depends on item size and tile (the parts of shared tiles),
+  // so every combination counts.  It grows with the streams, so their largest
+  // value covers them; item size and tile are the outer loops because only
+  // they rebuild the bins.
+  std::vector<int> chunks(std::begin(kTuneChunks), std::end(kTuneChunks));
+  std::vector<std::pair<int, int>> tiles;
+  for (const auto& tw : kTuneTiles) tiles.emplace_back(tw[0], tw[1]);
+  std::vector<int> budgets(std::begin(kTuneBudgets), std::end(kTuneBudgets));
+  const auto include = [](auto& v, const auto& x) {
+    if (std::find(v.begin(), v.end(), x) == v.end()) v.push_back(x);
+  };
+  include(chunks, keep.chunk);
+  include(tiles, std::make_pair(keep.tile_w, keep.tile_h));
+  include(budgets, keep.batch_mb);
+  size_t most = 0, b = 0;
   nr_status st = NR_OK;
-  // the slot areas of every batch budget and stream count at the current tile
-  for (int mb : kTuneBudgets)
-    for (int ns : kTuneStreams) {
-      nr::Tuning t = keep;
-      t.batch_mb = mb;
-      t.streams = ns;
-      if ((st = layout_bytes(plan, t, b)) != NR_OK) break;
-      most = std::max(most, b);
-    }
-  // and the tables of every tile shape at the smallest item size
-  for (const auto& tw : kTuneTiles) {
-    if (st != NR_OK) break;
-    nr::Tuning t = keep;
-    t.tile_w = tw[0];
-    t.tile_h = tw[1];
-    t.chunk = kTuneChunks[0];
-    if ((st = layout_bytes(plan, t, b)) != NR_OK) break;
-    tables = std::max(tables, plan->p.off_slot);
-  }
+  for (int c : chunks)
+    for (const auto& tile : tiles)
+      for (int mb : budgets) {
+        if (st != NR_OK) break;
+        nr::Tuning t = keep;
+        t.chunk = c;
+        t.tile_w = tile.first;
+        t.tile_h = tile.second;
+        t.batch_mb = mb;
+        t.streams = std::max(keep.streams, *std::max_element(std::begin(kTuneStreams), std::end(kTuneStreams)));
+        if ((st = layout_bytes(plan, t, b, true)) == NR_OK) most = std::max(most, b);
+      }
   plan->p.tune = keep;
   plan->p.laid_out = false;
   std::string err;
   if (was_laid_out || st == NR_OK) (void)nr::layout_plan(plan->p, err);
   if (st != NR_OK) return st;
-  *bytes = tune_buffer_bytes(plan->p) + most + tables + (size_t(1) << 20);
+  *bytes = tune_buffer_bytes(plan->p) + most + (size_t(1) << 20);
   return NR_OK;
 }
 

@@ -176,7 +176,7 @@ int item_points(const Plan& plan, int64_t items) {
   return int(std::min<int64_t>(plan.tune.chunk, c));
 }
 
-void build_spread_bins(const Plan& plan, Geom& g) {
+void build_spread_bins(const Plan& plan, Geom& g, bool bounds) {
   const int W = plan.kb.W;
   const int na = g.key.n_angles;
   // tile shape from the tuning (compiled shapes only); edge tiles are partial
@@ -254,7 +254,7 @@ void build_spread_bins(const Plan& plan, Geom& g) {
       // magnitude of every cell's sum for the kernel's fixed-point scale
       std::fill(cell_count.begin(), cell_count.end(), 0);
       int cmax = 0;
-      for (int q = ib; q < ie; ++q) {
+      for (int q = ib; bounds && q < ie; ++q) {
         const int a = g.pts[size_t(q)] >> g.jbits, j = g.pts[size_t(q)] & ((1 << g.jbits) - 1);
         const int g0x = int(std::ceil(double(j) * g.gxy[2 * a] - halfW));
         const int g0y = int(std::ceil(double(j) * g.gxy[2 * a + 1] - halfW));
@@ -536,7 +536,7 @@ SliceScratch slice_scratch(const Geom& g) {
 
 }  // namespace
 
-nr_status layout_plan(Plan& plan, std::string& err) {
+nr_status layout_plan(Plan& plan, std::string& err, bool sizes_only) {
   if (plan.laid_out) return NR_OK;
   const Tuning& tu = plan.tune;
   if (!spread_tile_supported(tu.tile_w, tu.tile_h)) {
@@ -549,8 +549,10 @@ nr_status layout_plan(Plan& plan, std::string& err) {
     return NR_INVALID_ARG;
   }
   for (Geom& g : plan.geoms) {
-    if (g.bins_tile_w != tu.tile_w || g.bins_tile_h != tu.tile_h || g.bins_chunk != tu.chunk) {
-      build_spread_bins(plan, g);
+    if (g.bins_tile_w != tu.tile_w || g.bins_tile_h != tu.tile_h || g.bins_chunk != tu.chunk ||
+        !(g.bins_bounds || sizes_only)) {
+      build_spread_bins(plan, g, !sizes_only);
+      g.bins_bounds = !sizes_only;
       g.bins_tile_w = tu.tile_w;
       g.bins_tile_h = tu.tile_h;
       g.bins_chunk = tu.chunk;
@@ -822,7 +824,7 @@ nr_status layout_plan(Plan& plan, std::string& err) {
   for (size_t b = 0; b < plan.batches.size(); ++b) plan.batches[b].lane = int(b % size_t(plan.n_lanes));
   plan.off_slot = off;
   plan.ws_bytes = plan.off_slot + size_t(plan.n_lanes) * plan.slot_area;
-  plan.laid_out = true;
+  plan.laid_out = !sizes_only;
   return NR_OK;
 }
 

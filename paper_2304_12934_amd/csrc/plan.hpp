@@ -80,6 +80,7 @@ struct Geom {
   // tuning the bins were last built for (layouts that change only the
   // batching reuse them)
   int bins_tile_w = -1, bins_tile_h = -1, bins_chunk = -1, ibins_chunk = -1;
+  bool bins_bounds = false;         // the spreading items' cell-count bounds are set
   // workspace offsets (bytes)
   size_t off_gxy = 0, off_flip = 0, off_pts = 0, off_items = 0, off_shared = 0, off_ipts = 0, off_iitems = 0;
 };
@@ -173,8 +174,10 @@ nr_status build_plan(const nr_slice* slices, int32_t n_slices, const double* ang
                      const nr_nufft* params, Plan& plan, std::string& err);
 
 // Spreading bins (for the current tuning), batches, work lists and the
-// workspace layout.  Idempotent until the tuning changes.
-nr_status layout_plan(Plan& plan, std::string& err);
+// workspace layout.  Idempotent until the tuning changes.  With sizes_only the
+// workspace is sized (ws_bytes) but the plan is not laid out for use: the cell
+// counts that bound the spreading items' sums, most of the work, are left out.
+nr_status layout_plan(Plan& plan, std::string& err, bool sizes_only = false);
 
 // FFT lengths the persistent kernel is built for (128..4096, powers of two).
 bool persist_length_supported(int L);
@@ -190,8 +193,9 @@ int disc_radius(const Plan& plan, const Geom& g);
 // would make fewer than `items` items.
 int item_points(const Plan& plan, int64_t items);
 
-// Fills the spreading bins of one geometry (called by layout_plan).
-void build_spread_bins(const Plan& plan, Geom& g);
+// Fills the spreading bins of one geometry (called by layout_plan), with or
+// without the items' bounds.
+void build_spread_bins(const Plan& plan, Geom& g, bool bounds = true);
 
 // Fills the interpolation bins of one geometry (called by layout_plan).
 void build_interp_bins(const Plan& plan, Geom& g);

@@ -506,6 +506,24 @@ __global__ __launch_bounds__(256) void k_mbir_extrapolate(float* y, const float*
   for_each_group<V, true>(count, MbirExtrapolate{y, x, x_prev, float(state[kStBeta])});
 }
 
+// The whole update in one pass once the momentum is known, x' formed again, the
+// stores in the order y, x_prev, x: for calls whose x, x_prev or y are one
+// buffer (a caller that keeps no x_prev passes x for it), where a step taken in
+// the dot pass would lose the values this pass needs.
+__global__ __launch_bounds__(256) void k_mbir_update_in_order(float* x, float* x_prev, float* y, const float* g,
+                                                              size_t count, float inv_L, int nonneg,
+                                                              const double* __restrict__ state) {
+  const float beta = float(state[kStBeta]);
+  for (size_t i = size_t(blockIdx.x) * 256 + threadIdx.x; i < count; i += size_t(gridDim.x) * 256) {
+    float xn = y[i] - inv_L * g[i];
+    if (nonneg) xn = fmaxf(xn, 0.f);
+    const float xo = x[i];
+    y[i] = xn + beta * (xn - xo);
+    x_prev[i] = xo;
+    x[i] = xn;
+  }
+}
+
 // Monotone update, the candidate x' held in x_prev: accepted, x <- x',
 // x_prev <- x, y <- x' + beta (x' - x); rejected, x stays and y = x_prev = x.
 __global__ __launch_bounds__(256) void k_mbir_update_mono(float* __restrict__ x, float* __restrict__ x_prev,
@@ -657,6 +675,15 @@ hipError_t launch_mbir_extrapolate(float* y, const float* x, const float* x_prev
 hipError_t launch_mbir_update(float* x, float* x_prev, float* y, float* g, size_t count, float inv_L,
                               int nonneg, int restart, double* state, hipStream_t st, bool add_x_prev) {
   hipLaunchKernelGGL(k_set_double, dim3(1), dim3(1), 0, st, state + kStDot, 0.0);
+  if (x == x_prev || x == y || x_prev == y) {
+    if (const hipError_t e = mbir_dot<false>(x, y, g, count, inv_L, nonneg, state, nullptr,
+                                             add_x_prev ? x_prev : nullptr, st))
+      return e;
+    hipLaunchKernelGGL(k_mbir_finalize, dim3(1), dim3(1), 0, st, state, restart, 0);
+    hipLaunchKernelGGL(k_mbir_update_in_order, dim3(pass_blocks(count, 1, 4096)), dim3(256), 0, st, x, x_prev, y, g,
+                       count, inv_L, nonneg, state);
+    return hipGetLastError();
+  }
   if (const hipError_t e = mbir_dot<true>(x, y, g, count, inv_L, nonneg, state, x_prev, add_x_prev ? x_prev : nullptr, st))
     return e;
   hipLaunchKernelGGL(k_mbir_finalize, dim3(1), dim3(1), 0, st, state, restart, 0);

@@ -57,3 +57,31 @@ def test_item_sizes_against_oracle(n, na, z):
     else:
         pix = rng.integers(n // 8, n - n // 8, (64, 2))
         assert rel([g[z - 1][iy, ix] for iy, ix in pix], ora.radon_adj_entries(y[z - 1], ang, n, pix)) < 1e-5
+
+
+@pytest.mark.parametrize("width", [6, 7, 8])
+def test_two_items_per_workgroup_equal_one(width):
+    """A launch of at least 8192 interpolation and spreading items (two per
+    workgroup) against launches of one slice each (one per workgroup) over the
+    same items: every item's arithmetic is the same, so the forward is equal bit
+    for bit, and the adjoint differs by no more than float32 rounding."""
+    from paper_2304_12934_amd import Plan
+    n, na, z = 1024, 200, 12
+    print(f"case: {z} x {n}^2, {na} angles, width {width}, two items and one per workgroup", flush=True)
+    ang = np.linspace(0, np.pi, na, endpoint=False)
+    # interpolation items: tiles of 32 x 64 cells holding first taps (radius j G / N_t of the half plane)
+    j = np.arange(n // 2 + 1) * 2.0
+    u, v = np.abs(np.outer(np.sin(ang), j)), np.outer(np.cos(ang), j)
+    assert z * len(np.unique(np.floor(u / 32) * 1000 + np.floor(v / 64))) >= 9000
+    dev = torch.device("cuda", 0)
+    vol = torch.as_tensor(np.random.default_rng(width).uniform(0, 1, (z, n, n)), dtype=torch.float32, device=dev)
+    sino = torch.as_tensor(np.random.default_rng(9).standard_normal((z, na, n)), dtype=torch.float32, device=dev)
+    out = []
+    for tuning in ({"batch_mb": 2048, "streams": 1}, {"batch": 1, "streams": 1}):
+        with Plan.uniform_stack(n, n, ang, z, width=width, device=dev, tuning=tuning) as plan:
+            info = plan.info()
+            assert info["batches"] == (1 if "batch_mb" in tuning else z)
+            assert z * info["spread_items"] >= 9000
+            out.append((plan.fwd(vol), plan.adj(sino)))
+    assert torch.equal(out[0][0], out[1][0])
+    assert float((out[0][1] - out[1][1]).norm() / out[1][1].norm()) <= 1e-6

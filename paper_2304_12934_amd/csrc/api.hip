@@ -960,8 +960,9 @@ nr_status mbir_step(nr_plan* plan, const nr_prior* prior, const nr_mbir* params,
   hipError_t e = hipSuccess;
   if (!params->monotone) {
     // The prior gradient (arithmetic-bound) runs beside the projector
-    // (memory-bound) on the plan's prior stream, into d_x_prev: the update
-    // overwrites d_x_prev without reading it, and adds it to d_grad first.
+    // (memory-bound) on the plan's prior stream, into d_x_prev: the update's
+    // first pass reads it there, adds it to d_grad and only then stores x_k in
+    // its place.
     // While stages are timed, it runs on st before the projector instead.
     const bool prior_on = prior->lambda > 0.0f;
     const bool side = prior_on && !plan->profiling;

@@ -19,8 +19,11 @@ enum { kItemPart = 1, kItemDC = 2 };
 struct SharedTile {
   int32_t tile, first, count;
 };
-// units of work a shared tile's parts are added up in (each a fourth of its rows)
-constexpr int kSharedTileUnits = 4;
+// A shared tile's parts are added up in units, numbered tile kSharedUnitsMax +
+// unit in the tile: four, a thread adding every part of its cells, or, with more
+// than kSharedSplitParts parts, kSharedUnitsMax of fewer cells whose parts are
+// split among the threads.
+constexpr int kSharedUnits = 4, kSharedUnitsMax = 64, kSharedSplitParts = 16;
 
 // Interpolation tiles: a point belongs to the tile holding its first tap; the
 // kernel stages the tile plus W + 1 cells (the footprint and a one-cell

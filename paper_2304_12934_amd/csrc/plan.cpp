@@ -697,7 +697,9 @@ nr_status layout_plan(Plan& plan, std::string& err, bool sizes_only) {
          }))
       bt.adj.push_back(sl);
     add(bt.adj, Stage::SpreadShared, 0, true, false, [](int s, const Geom& g, std::vector<WorkItem>& v) {
-      for (int u = 0; u < kSharedTileUnits * int(g.shared.size()); ++u) v.push_back({s, u});
+      for (int t = 0; t < int(g.shared.size()); ++t)
+        for (int u = 0; u < (g.shared[size_t(t)].count > kSharedSplitParts ? kSharedUnitsMax : kSharedUnits); ++u)
+          v.push_back({s, t * kSharedUnitsMax + u});
     });
     for (int G : Gs) add(bt.adj, Stage::AdjCols, G, true, true, columns);
     for (int G : Gs) add(bt.adj, Stage::AdjRows, G, true, true, row_pairs);

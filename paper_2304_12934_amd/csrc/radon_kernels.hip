@@ -868,45 +868,69 @@ __global__ void k_fill_zero(float4* p, size_t n4) {
     p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-// Adds up the parts of a tile that several items share, in their order: unit u
-// is one fourth of the rows of shared tile u / 4.  Bound by reading the parts
-// (2560^2, 1024 angles: 422 parts of 162 tiles, 9 MB read and written, 2.3 us
-// per slice; sixteen-fold smaller units ran 4.2); the loads of eight parts are
-// in flight at once for the tile at the origin, whose parts number in the
-// tens.  The parts replace global float atomics into a cleared tile, which
+// Adds up the parts of a tile that several items share, always in the same
+// order.  Bound by reading the parts (2560^2, 1024 angles: 422 parts of 162
+// tiles, 9 MB read and written, 1.9 us per slice), a fourth of a tile per
+// workgroup and eight parts in flight per thread (sixteen-fold smaller units ran
+// 4.2 us).  A tile of many parts (small slices under long detectors) would make
+// that a chain of loads on a few workgroups: beyond kSharedSplitParts parts, 64
+// workgroups take a tile and their threads a share of its parts.  Between events
+// (6 us of them), two 64^2 slices of 300 angles x 5120 bins (some 80 parts per tile) 41 -> 11 us, one of 3200 x
+// 2560 187 -> 20; eight 2560^2 slices the same.  The line: with it at 8, 16, 32
+// and 64 parts, two 128^2 slices of 300 x 2560 took 7.7, 8.1, 8.9 and 11.3 us,
+// two 256^2 ones of 300 x 5120 12.1, 11.1, 11.3 and 12.4.  The parts replace global float atomics into a cleared tile, which
 // meet in the memory behind the XCDs' caches: the sums no longer depend on the
 // order of arrival, and cutting a tile costs a write and a read of its cells
 // per part (four 1024^2 slices of 901 angles: whole adjoint 139 -> 124 us; seven
 // 320^2 slices of 451: 79 -> 58).
 template <int TW, int TH, class LA>
-__device__ __forceinline__ void spread_shared_unit(const LA& a, const WorkItem wi, const int tid) {
+__device__ __forceinline__ void spread_shared_unit(const LA& a, const WorkItem wi, float2* lds, const int tid) {
   const DSlice d = load_desc(a.descs, wi.slice);
-  const int u = __builtin_amdgcn_readfirstlane(wi.unit);
-  const NR_C SharedTile& sh = d.shared[u / kSharedTileUnits];
+  const int unit = __builtin_amdgcn_readfirstlane(wi.unit), u = unit % kSharedUnitsMax;
+  const NR_C SharedTile& sh = d.shared[unit / kSharedUnitsMax];
   const int t = sh.tile, first = sh.first, count = sh.count;
-  constexpr int CELLS = TW * TH / kSharedTileUnits, PER = CELLS / 256;
-  static_assert(TH % kSharedTileUnits == 0 && CELLS % 256 == 0, "whole rows, whole rounds");
-  const int c0 = (u % kSharedTileUnits) * CELLS;
-  const NR_G float2* __restrict__ p = d.parts + size_t(first) * (TW * TH) + c0 + tid;
-  float2 sum[PER];
-#pragma unroll
-  for (int z = 0; z < PER; ++z) sum[z] = make_float2(0.f, 0.f);
-#pragma unroll 8
-  for (int k = 0; k < count; ++k)
-#pragma unroll
-    for (int z = 0; z < PER; ++z) sum[z] = c_add(sum[z], p[k * (TW * TH) + z * 256]);
   const int r0 = (t / d.tiles_x) * TH, cc0 = (t % d.tiles_x) * TW;
-#pragma unroll
-  for (int z = 0; z < PER; ++z) {
-    const int c = c0 + tid + z * 256;
+  const auto store = [&](int c, float2 sum) {
     const int r = r0 + c / TW, cc = cc0 + c % TW;
-    if (r < d.rows && cc < d.cols) d.ext[size_t(r) * d.cols + cc] = sum[z];
+    if (r < d.rows && cc < d.cols) d.ext[size_t(r) * d.cols + cc] = sum;
+  };
+  const NR_G float2* __restrict__ p = d.parts + size_t(first) * (TW * TH);
+  if (count <= kSharedSplitParts) {
+    constexpr int CELLS = TW * TH / kSharedUnits, PER = CELLS / 256;
+    static_assert(TW * TH % kSharedUnits == 0 && CELLS % 256 == 0, "whole rounds");
+    const int c0 = u * CELLS + tid;
+    float2 sum[PER];
+#pragma unroll
+    for (int z = 0; z < PER; ++z) sum[z] = make_float2(0.f, 0.f);
+#pragma unroll 8
+    for (int k = 0; k < count; ++k)
+#pragma unroll
+      for (int z = 0; z < PER; ++z) sum[z] = c_add(sum[z], p[size_t(k) * (TW * TH) + c0 + z * 256]);
+#pragma unroll
+    for (int z = 0; z < PER; ++z) store(c0 + z * 256, sum[z]);
+  } else {
+    // thread (group, cell): parts group, group + GROUPS, ...; the groups' sums
+    // are then added in order
+    constexpr int CELLS = TW * TH / kSharedUnitsMax, GROUPS = 256 / CELLS;
+    static_assert(CELLS * GROUPS == 256, "whole groups");
+    const int cell = tid % CELLS, c = u * CELLS + cell;
+    float2 sum = make_float2(0.f, 0.f);
+#pragma unroll 8
+    for (int k = tid / CELLS; k < count; k += GROUPS) sum = c_add(sum, p[size_t(k) * (TW * TH) + c]);
+    lds[tid] = sum;
+    __syncthreads();
+    if (tid < CELLS) {
+#pragma unroll
+      for (int g = 1; g < GROUPS; ++g) sum = c_add(sum, lds[g * CELLS + cell]);
+      store(c, sum);
+    }
   }
 }
 
 template <int TW, int TH>
 __global__ __launch_bounds__(256) void k_spread_shared(LaunchArgs a) {
-  NR_FOR_EACH_UNIT(a, wi) spread_shared_unit<TW, TH>(a, wi, int(threadIdx.x));
+  __shared__ float2 lds[256];
+  NR_FOR_EACH_UNIT(a, wi) spread_shared_unit<TW, TH>(a, wi, lds, int(threadIdx.x));
 }
 
 // One work item = one grid tile (TH rows x TW columns) and a range of the
@@ -1399,7 +1423,7 @@ __device__ __forceinline__ void persist_unit(const LA& a, const KB& kb, int stag
       }
       return;
     case StageKind::SpreadShared:
-      spread_shared_unit<64, 32>(a, wi, tid);
+      spread_shared_unit<64, 32>(a, wi, f2, tid);
       return;
     case StageKind::Spread: {
       spread_tiles_unit<W, 64, 32, kPersistThreads>(a, kb, wi, reinterpret_cast<int*>(lds), red, nonfinite, tid);

@@ -54,7 +54,7 @@ struct SliceDesc {
   const int32_t* pts;             // spreading point lists (tile-major)
   const SpreadItem* items;        // spreading work items of this slice's geometry
   const SharedTile* shared;       // tiles that several items share
-  float* parts;                   // [part][tile_h][tile_w] complex: the sums of their items (T's memory, dead meanwhile)
+  float* parts;                   // [part][tile_h][tile_w] complex: the sums of their items (may lie in T's memory, dead meanwhile)
   const int32_t* ipts;            // interpolation point lists (tile-major, every point once)
   const SpreadItem* iitems;       // interpolation work items (tile, point range)
 };

@@ -511,26 +511,30 @@ void append_units_by_cost(std::vector<WorkItem>& out, const std::vector<WorkItem
     for (const auto& r : run) out.push_back(k < r.size() ? r[k] : WorkItem{-1, 0});
 }
 
-// Scratch of one slice: ext, yh, and one area for T (its q rows rounded up to a
-// multiple of 4) and the parts of the shared tiles, each 256-byte aligned
-// (offsets in bytes).  T and the parts never live at the same time: the
-// forward's columns have read T before a spreading starts, and the adjoint's
-// columns write it after the parts are added up, so parts take memory, and a
-// share of a batch's budget, only beyond T's size.  (In an area of their own
-// they cut batches short: sixteen 512^2 slices of 720 angles went from one
-// batch to two and their forward from 104 to 127 us.)
+// Scratch of one slice: ext, yh, T (its q rows rounded up to a multiple of 4)
+// and the parts of the shared tiles, each 256-byte aligned (offsets in bytes).
+// T and the parts never live at the same time: the forward's columns have read
+// T before a spreading starts, and the adjoint's columns write it after the
+// parts are added up.  Where parts of their own would cut batches short, they
+// lie in T's memory and take scratch only beyond its size: sixteen 512^2 slices
+// of 720 angles run in one batch instead of two (forward 127 -> 96 us, adjoint
+// 187 -> 154), sixteen 1280^2 of 1024 angles in less memory (adjoint 608 -> 584).
+// A stack that fits one batch either way keeps them apart, which measured a
+// little faster (seven 320^2 slices, adjoint 54.7 and 53.8 us; sixteen 512^2 of
+// 400 angles, forward 90.7 and 89.3).
 struct SliceScratch {
-  size_t yh, T, bytes;
+  size_t yh, T, parts, bytes;
   size_t grids;   // T, ext and yh alone
 };
-SliceScratch slice_scratch(const Geom& g) {
+SliceScratch slice_scratch(const Geom& g, bool parts_apart) {
   SliceScratch o{};
   const size_t t_bytes = size_t((g.G / 2 + 4) / 4 * 4) * g.key.n * sizeof(f2);
   const size_t part_bytes = size_t(g.n_parts) * g.tile_w * g.tile_h * sizeof(f2);
   o.yh = align_up(size_t(g.rows) * g.cols * sizeof(f2), 256);
   o.T = align_up(o.yh + size_t(g.key.n_angles) * g.H * sizeof(f2), 256);
   o.grids = align_up(o.T + t_bytes, 256);
-  o.bytes = align_up(o.T + std::max(t_bytes, part_bytes), 256);
+  o.parts = parts_apart ? o.grids : o.T;
+  o.bytes = std::max(o.grids, align_up(o.parts + part_bytes, 256));
   return o;
 }
 
@@ -583,6 +587,9 @@ nr_status layout_plan(Plan& plan, std::string& err, bool sizes_only) {
   // larger than the budget runs alone); a budget of one slot's size keeps each
   // slice's grids resident in the 256 MB last-level cache between stages
   const size_t budget = size_t(tu.batch_mb) << 20;
+  size_t whole = 0;   // the plan's scratch with the parts apart
+  for (int gi : plan.slice_geom) whole += slice_scratch(plan.geoms[size_t(gi)], true).bytes;
+  plan.parts_apart = whole <= budget && (tu.batch == 0 || ns <= tu.batch);
   plan.batches.clear();
   plan.work.clear();
   plan.slot_area = 0;
@@ -592,7 +599,7 @@ nr_status layout_plan(Plan& plan, std::string& err, bool sizes_only) {
     size_t used = 0;
     for (int s = b0; s < ns; ++s) {
       const Geom& g = plan.geoms[size_t(plan.slice_geom[size_t(s)])];
-      const SliceScratch sc = slice_scratch(g);
+      const SliceScratch sc = slice_scratch(g, plan.parts_apart);
       const size_t need = sc.bytes;
       if (!bt.slices.empty() && (used + need > budget || (tu.batch > 0 && int(bt.slices.size()) >= tu.batch)))
         break;
@@ -861,11 +868,11 @@ std::vector<SliceDesc> slice_descs(const Plan& plan, char* d_ws) {
       d.gxy = reinterpret_cast<const double*>(d_ws + g.off_gxy);
       d.flip = reinterpret_cast<const int32_t*>(d_ws + g.off_flip);
       char* slot = d_ws + plan.off_slot + size_t(bt.lane) * plan.slot_area + bt.slot_off[k];
-      const SliceScratch sc = slice_scratch(g);
+      const SliceScratch sc = slice_scratch(g, plan.parts_apart);
       d.ext = reinterpret_cast<float*>(slot);
       d.yh = reinterpret_cast<float*>(slot + sc.yh);
       d.T = reinterpret_cast<float*>(slot + sc.T);
-      d.parts = d.T;
+      d.parts = reinterpret_cast<float*>(slot + sc.parts);
       d.pts = reinterpret_cast<const int32_t*>(d_ws + g.off_pts);
       d.items = reinterpret_cast<const SpreadItem*>(d_ws + g.off_items);
       d.shared = reinterpret_cast<const SharedTile*>(d_ws + g.off_shared);

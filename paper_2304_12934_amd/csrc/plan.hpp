@@ -157,6 +157,7 @@ struct Plan {
   size_t slot_area = 0;             // bytes of the largest batch's scratch (one area per lane)
   int n_lanes = 1;                  // concurrent streams in use (at most the number of batches)
   int n_slots = 0;                  // most slices in one batch
+  bool parts_apart = false;         // parts of shared tiles in memory of their own, not in T's
   size_t ws_bytes = 0;
   // persistent launches: every batch's entries, its tables, the sync area
   // (int32: the error flag at 0, then each batch's tickets and counters)

@@ -297,9 +297,10 @@ nr_status run_batches(nr_plan* plan, bool fwd, const float* b, bool adj, const f
     hipStream_t bs = lane_stream(bt);
     // a forward whose sinogram is the adjoint's input: the forward's radial
     // stage runs the adjoint's too (while stages are timed, each on its own).
-    // The joined kernel saves a launch and a read of the rows but keeps 10
-    // wavefronts per CU where the two keep 16, which long stages feel more: us
-    // per radon_normal, joined and not, 128^2 (0.02 M points of radial lines)
+    // The joined kernel saves a launch and a read of the rows but holds more
+    // registers (at 2560 points 92, for five wavefronts per SIMD, where each of
+    // the two holds 44, for eight), which long stages feel more: us per
+    // radon_normal, joined and not, 128^2 (0.02 M points of radial lines)
     // 39 and 41, 16 x 512^2 (1.6 M) 179 and 185, 8 x 2048^2 (3.0 M) 817 and
     // 824, 8 x 1024^2 (3.7 M) 364 and 364, 32 x 1280^2 (5.2 M) 1415 and 1406,
     // 8 x 2560^2 (10.5 M) 1528 and 1503.

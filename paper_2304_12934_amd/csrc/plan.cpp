@@ -168,6 +168,10 @@ int disc_radius(const Plan& plan, const Geom& g) {
 // tile add a write and a read of its cells each: 181 angles of a 128^2 slice
 // 16.5 -> 10.5 us, 180 of a 256^2 slice 16.8 -> 10.5; with 256 items sixteen
 // 512^2 slices and four 1024^2 ones run the same, one 1280^2 slice slower.
+// The points are those of the whole plan: a plan of many slices keeps large items
+// also where its batches hold one slice each (sizing them by the batch is not
+// measured).  The fixed-point scale is an item's, so the last bits of a slice's
+// adjoint depend on which slices share its plan.
 int item_points(const Plan& plan, int64_t items) {
   int64_t points = 0;
   for (int gi : plan.slice_geom) points += int64_t(plan.geoms[size_t(gi)].key.n_angles) * plan.geoms[size_t(gi)].H;

@@ -190,8 +190,8 @@ std::vector<SliceDesc> slice_descs(const Plan& plan, char* d_ws);
 // spreading tap lands and no interpolation tap reads.
 int disc_radius(const Plan& plan, const Geom& g);
 
-// Most points per item of a plan: the tuning's, or fewer where the plan's points
-// would make fewer than `items` items.
+// Most points per item of a plan: the tuning's, or fewer where the points of all
+// the plan's slices would make fewer than `items` items.
 int item_points(const Plan& plan, int64_t items);
 
 // Fills the spreading bins of one geometry (called by layout_plan), with or

@@ -875,14 +875,16 @@ __global__ void k_fill_zero(float4* p, size_t n4) {
 // 4.2 us).  A tile of many parts (small slices under long detectors) would make
 // that a chain of loads on a few workgroups: beyond kSharedSplitParts parts, 64
 // workgroups take a tile and their threads a share of its parts.  Between events
-// (6 us of them), two 64^2 slices of 300 angles x 5120 bins (some 80 parts per tile) 41 -> 11 us, one of 3200 x
-// 2560 187 -> 20; eight 2560^2 slices the same.  The line: with it at 8, 16, 32
-// and 64 parts, two 128^2 slices of 300 x 2560 took 7.7, 8.1, 8.9 and 11.3 us,
-// two 256^2 ones of 300 x 5120 12.1, 11.1, 11.3 and 12.4.  The parts replace global float atomics into a cleared tile, which
+// (6 us of them), two 64^2 slices of 300 angles x 5120 bins (some 80 parts per
+// tile) 41 -> 11 us, one of 3200 x 2560 187 -> 20; eight 2560^2 slices the same.
+// The line: with it at 8, 16, 32 and 64 parts, two 128^2 slices of 300 x 2560
+// took 7.7, 8.1, 8.9 and 11.3 us, two 256^2 ones of 300 x 5120 12.1, 11.1, 11.3
+// and 12.4.  The parts replace global float atomics into a cleared tile, which
 // meet in the memory behind the XCDs' caches: the sums no longer depend on the
-// order of arrival, and cutting a tile costs a write and a read of its cells
-// per part (four 1024^2 slices of 901 angles: whole adjoint 139 -> 124 us; seven
-// 320^2 slices of 451: 79 -> 58).
+// order of arrival, and cutting a tile costs a write and a read of its cells per
+// part (four 1024^2 slices of 901 angles: whole adjoint 139 -> 124 us; seven
+// 320^2 slices of 451: 79 -> 58).  Large launches pay: eight 2560^2 adjoints 808
+// -> 818 us.
 template <int TW, int TH, class LA>
 __device__ __forceinline__ void spread_shared_unit(const LA& a, const WorkItem wi, float2* lds, const int tid) {
   const DSlice d = load_desc(a.descs, wi.slice);
@@ -1287,7 +1289,9 @@ __device__ __forceinline__ void adj_cols_unit(const LA& a, const WorkItem wi, fl
 
 // wavefronts per SIMD the adjoint transforms are compiled for: with the split
 // exchange six (80 VGPRs; seven spill a few at L = 5120 and ran slower), with
-// the three-pass plans seven (72)
+// the three-pass plans seven (72 VGPRs; 61 to 71 are used, and seven or eight
+// reside at 1280 and 2560 points, while at 1024 and 2048 the LDS, 8 KB for one
+// wavefront and 16 for two, admits five)
 constexpr int store_out_waves(int L) { return split_exchange_length(L) ? 6 : (adjoint_plan_differs(L) ? 7 : 1); }
 
 template <int L>
@@ -1554,7 +1558,13 @@ hipError_t launch(K kernel, int threads, int n, hipStream_t st, Args... args) {
 // resident workgroups, the parallelism is worth more: us per slice, paired and
 // not, of one 2560^2 slice (5440 items) spreading 60.8 and 54.4, interpolation
 // 58.3 and 50.8; of 2048^2 (361 angles) spreading 33.7 and 29.1; of 1280^2
-// (256 angles) 16.4 and 13.3; of 64^2 (45 angles) 4.3 and 3.2
+// (256 angles) 16.4 and 13.3; of 64^2 (45 angles) 4.3 and 3.2; whole adjoint of
+// sixteen 1280^2 slices (1024 angles, 4779 items per launch) 745 and 703.  From
+// 8192 to some 20,000 items neither leads by more than 4 %: one is faster where
+// items are full (adjoint of eight and sixteen 1024^2 slices, 901 angles, 8520
+// and 17,040 items: 207 and 200, 393 and 388), two where they are light (six
+// 2048^2, 361 angles, 20,200 items: 339 and 347; four 2560^2, 21,760: 435 and
+// 443)
 constexpr int kPairItemsMin = 8192;
 
 template <int W>

@@ -1504,8 +1504,12 @@ __global__ __launch_bounds__(kPersistThreads) void k_persistent(PersistLaunch ar
         break;
       }
     }
-    // the producers' stores are in this XCD's L2; drop stale lines from L1
-    asm volatile("buffer_inv sc0" ::: "memory");
+    // The producers' stores are in this XCD's L2; drop stale lines from L1: the
+    // adjoint's stages overwrite yh, the grid and T, which the forward's read on
+    // this CU before.  The producers are other workgroups, so the scope is the
+    // agent's: a workgroup-scope invalidate (buffer_inv sc0) does nothing where a
+    // workgroup stays on one CU.
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     // the launch and kernel arguments are read where each unit uses them
     // (scalar loads from the argument segment), not held in registers across
     // the loop: the laundered pointer is not loop-invariant to the compiler

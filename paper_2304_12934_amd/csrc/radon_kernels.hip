@@ -562,6 +562,11 @@ __device__ __forceinline__ void fwd_interp_unit(const LA& a, const KB& kb, const
   for (int j = tid; j <= L / 2; j += T) {
     float2 X = c_scale(interp_point<W>(d, a.halo, a.colpad, kb, a0, j), inv);
     float2 Y = has1 ? c_scale(interp_point<W>(d, a.halo, a.colpad, kb, a1, j), inv) : make_float2(0.f, 0.f);
+    if (d.shift) {   // rotation axis at bin L/2 + c: evaluate the line at t - c
+      const float2 p = d.shift[j];
+      X = c_mul(X, p);
+      Y = c_mul(Y, p);
+    }
     if (j == 0 || j == L / 2) {   // the full line's sum is real: keep Re at k = 0 and k = -1/2
       X.y = 0.f;
       Y.y = 0.f;

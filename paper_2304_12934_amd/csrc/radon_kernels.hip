@@ -1294,10 +1294,12 @@ __device__ __forceinline__ void adj_cols_unit(const LA& a, const WorkItem wi, fl
 
 // wavefronts per SIMD the adjoint transforms are compiled for: with the split
 // exchange six (80 VGPRs; seven spill a few at L = 5120 and ran slower), with
-// the three-pass plans seven (72 VGPRs; 61 to 71 are used, and seven or eight
-// reside at 1280 and 2560 points, while at 1024 and 2048 the LDS, 8 KB for one
-// wavefront and 16 for two, admits five)
-constexpr int store_out_waves(int L) { return split_exchange_length(L) ? 6 : (adjoint_plan_differs(L) ? 7 : 1); }
+// the three-pass plans seven (72 VGPRs; 61 to 71 are used) at 640, 1280 and 2560
+// points and five at 1024 and 2048, where the LDS, 8 KB for one wavefront and 16
+// for two, admits no more
+constexpr int store_out_waves(int L) {
+  return split_exchange_length(L) ? 6 : (L == 1024 || L == 2048 ? 5 : (adjoint_plan_differs(L) ? 7 : 1));
+}
 
 template <int L>
 __global__ __launch_bounds__(adj_threads(L)) __attribute__((amdgpu_waves_per_eu(store_out_waves(L)))) void k_adj_cols(
